@@ -13,14 +13,17 @@
 // multiply-adds and the hardware square root.  It tracks the smallest and
 // second smallest value as integer keys: the distance's bit pattern (a
 // non-negative float orders like its bits) with the low four bits replaced
-// by the candidate number, so one integer min and one median-of-three keep
-// both, and the smallest key names the candidate (lowest index first).  Each
-// fast value is within 11 u of the exact real distance and each reference
-// value within 4 u (u = 2^-24; relative, all terms are non-negative); the
-// keys drop at most 2^-19 relative.  So if the best key's distance is below
-// the second's by more than 2^-17 of the latter, the reference argmin is the
-// same candidate and no reference value ties with it.  Otherwise (near ties)
-// the pixel recomputes every candidate with the reference sequence.
+// by the candidate's place (4 row + column), so the smallest key names the
+// candidate, lowest index first.  The keys of each row of three candidates
+// give their smallest and middle in one instruction each, and the three rows'
+// results the smallest and second smallest of the nine (10 instructions for
+// the nine keys; a running pair took 27).  Each fast value is within 11 u of
+// the exact real distance and each reference value within 4 u (u = 2^-24;
+// relative, all terms are non-negative).  Keys 160 apart mean distances more
+// than 144 units in the last place apart, i.e. by more than 2^-17 of the
+// larger, so the reference argmin is the same candidate and no reference
+// value ties with it.  Otherwise (near ties) the pixel recomputes every
+// candidate with the reference sequence.
 //
 // Update, accumulation half: the pixel's colour enters its cluster's sums as
 // the exact integer rint(v * 2^18); x and y are integers.  A thread merges
@@ -44,7 +47,7 @@ namespace slic {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr float kCertify = 0x1p-17f;
+constexpr unsigned kCertify = 160;  // distance of two keys
 
 // Reference Eq. 1 distance: the exact operation sequence of the definition.
 __device__ __forceinline__ float eq1_reference(float cl, float ca, float cb, float cx, float cy,
@@ -72,6 +75,15 @@ __device__ __forceinline__ float eq1_fast(float cl, float ca, float cb, float cx
     const float dx = cx - xf;
     const float t = __builtin_fmaf(dx, dx, dy2);
     return __builtin_fmaf(wgt, __builtin_amdgcn_sqrtf(t), __builtin_amdgcn_sqrtf(s));
+}
+
+// Smallest and middle of three keys (the forms that compile to one
+// v_min3_u32 and one v_med3_u32).
+__device__ __forceinline__ unsigned umin3(unsigned a, unsigned b, unsigned c) {
+    return min(a, min(b, c));
+}
+__device__ __forceinline__ unsigned umed3(unsigned a, unsigned b, unsigned c) {
+    return max(min(a, b), min(max(a, b), c));
 }
 
 // Global (device) memory as a named address space: accesses through such
@@ -267,9 +279,9 @@ __global__ __launch_bounds__(kThreads, DIST == 0 ? 4 : 1) void assign_kernel(
     const bool col_ok = x < g.w;
 
     const int S = g.S;
-    const int gx_lo = x0 / S - 1, gy_lo = y0 / S - 1;
-    const int gx_hi = (min(x0 + Sh::kTileW, g.w) - 1) / S + 1;
-    const int gy_hi = (min(y0 + Sh::kTileH, g.h) - 1) / S + 1;
+    const int gx_lo = g.by_S.quotient(x0) - 1, gy_lo = g.by_S.quotient(y0) - 1;
+    const int gx_hi = g.by_S.quotient(min(x0 + Sh::kTileW, g.w) - 1) + 1;
+    const int gy_hi = g.by_S.quotient(min(y0 + Sh::kTileH, g.h) - 1) + 1;
     const int ncx = gx_hi - gx_lo + 1, ncy = gy_hi - gy_lo + 1, ncells = ncx * ncy;
     float4* cen4 = reinterpret_cast<float4*>(smem);
     float* ceny = reinterpret_cast<float*>(cen4 + ncells);
@@ -396,8 +408,8 @@ __global__ __launch_bounds__(kThreads, DIST == 0 ? 4 : 1) void assign_kernel(
     }
 
     // ---- prefetch this thread's pixels (they do not depend on the centres).
-    // Every lane loads (pixels outside the image read a clamped position and
-    // are then zeroed), so the loads are issued unconditionally.
+    // Every lane loads (pixels outside the image read a clamped position),
+    // so the loads are issued unconditionally.
     float pl[ROWS][VEC], pa[ROWS][VEC], pb[ROWS][VEC];
     {
         gmem<const float>* const Lg = as_global(g.L);
@@ -407,7 +419,6 @@ __global__ __launch_bounds__(kThreads, DIST == 0 ? 4 : 1) void assign_kernel(
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
             const int y = y0 + ty * ROWS + r;
-            const bool in = col_ok && y < g.h;
             const size_t pi = static_cast<size_t>(min(y, g.h - 1)) * g.w + xc;
             if constexpr (VEC == 4) {
                 const float4 l4 = load_f4(Lg + pi);
@@ -426,12 +437,6 @@ __global__ __launch_bounds__(kThreads, DIST == 0 ? 4 : 1) void assign_kernel(
                 pa[r][0] = Ag[pi];
                 pb[r][0] = Bg[pi];
             }
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                pl[r][v] = in ? pl[r][v] : 0.0f;
-                pa[r][v] = in ? pa[r][v] : 0.0f;
-                pb[r][v] = in ? pb[r][v] : 0.0f;
-            }
         }
     }
 
@@ -443,7 +448,8 @@ __global__ __launch_bounds__(kThreads, DIST == 0 ? 4 : 1) void assign_kernel(
         // one loop, each cell's loads and means together (the compiler then
         // overlaps the five FP64 divisions of a cell)
         for (int i = threadIdx.x; i < ncells; i += kThreads) {
-            const int cx = gx_lo + i % ncx, cy = gy_lo + i / ncx;
+            const int row = static_cast<int>((static_cast<float>(i) + 0.5f) * inv_ncx);
+            const int cx = gx_lo + (i - row * ncx), cy = gy_lo + row;
             for (int j = 0; j < 4; ++j) bins[j * ncells + i] = 0ull;
             if (cx < 0 || cy < 0 || cx >= g.ns_c || cy >= g.ns_r) {
                 // no centre here: an infinite colour distance never wins
@@ -483,14 +489,16 @@ __global__ __launch_bounds__(kThreads, DIST == 0 ? 4 : 1) void assign_kernel(
     // pixels of a row (they lie in one cell)
     // window column of the left candidates (columns past the image edge use the
     // tile's first cell, so every staged-window index stays in range)
-    const int gx_rel = (col_ok ? x / S : x0 / S) - gx_lo - 1;
+    const int gx_rel = g.by_S.quotient(col_ok ? x : x0) - gx_lo - 1;
     int cellv[ROWS][VEC];
+    int rowbase[ROWS];
     unsigned need = 0;  // pixels whose fast argmin is not certified: bit r * VEC + v
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
         const int y = y0 + ty * ROWS + r;
         const float yf = static_cast<float>(y);
-        const int base = (min(y, g.h - 1) / S - gy_lo - 1) * ncx + gx_rel;
+        const int base = (g.by_S.quotient(min(y, g.h - 1)) - gy_lo - 1) * ncx + gx_rel;
+        rowbase[r] = base;
         if constexpr (DIST == 1) {
             // exact: (distance bits, slot) as one 64-bit key, lowest slot on ties
             unsigned long long bk[VEC];
@@ -522,32 +530,38 @@ __global__ __launch_bounds__(kThreads, DIST == 0 ? 4 : 1) void assign_kernel(
             }
             continue;
         }
-        unsigned best[VEC], second[VEC];
+        // the keys of one row of candidates at a time: smallest and middle of
+        // three (one instruction each), then of the three rows
+        unsigned lo[3][VEC], mid[3][VEC];
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) best[v] = second[v] = 0xFFFFFFFFu;
+        for (int cr = 0; cr < 3; ++cr) {
+            unsigned key[3][VEC];
 #pragma unroll
-        for (int c = 0; c < 9; ++c) {
-            const int li = base + (c / 3) * ncx + (c % 3);
-            const float4 q = cen4[li];
-            const float dy = ceny[li] - yf;
-            const float dy2 = dy * dy;
+            for (int cc = 0; cc < 3; ++cc) {
+                const int li = base + cr * ncx + cc;
+                const float4 q = cen4[li];
+                const float dy = ceny[li] - yf;
+                const float dy2 = dy * dy;
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) {
+                    const float d = eq1_fast(q.x, q.y, q.z, q.w, dy2, pl[r][v], pa[r][v], pb[r][v],
+                                             static_cast<float>(x + v), g.wgt);
+                    key[cc][v] = (__float_as_uint(d) & ~15u) | static_cast<unsigned>(4 * cr + cc);
+                }
+            }
 #pragma unroll
             for (int v = 0; v < VEC; ++v) {
-                const float d = eq1_fast(q.x, q.y, q.z, q.w, dy2, pl[r][v], pa[r][v], pb[r][v],
-                                         static_cast<float>(x + v), g.wgt);
-                const unsigned key = (__float_as_uint(d) & ~15u) | static_cast<unsigned>(c);
-                // median of (best, second, key) given best <= second
-                second[v] = max(best[v], min(second[v], key));
-                best[v] = min(best[v], key);
+                lo[cr][v] = umin3(key[0][v], key[1][v], key[2][v]);
+                mid[cr][v] = umed3(key[0][v], key[1][v], key[2][v]);
             }
         }
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
-            const int slot = static_cast<int>(best[v] & 15u);
-            const float bf = __uint_as_float(best[v] & ~15u);
-            const float sf = __uint_as_float(second[v] & ~15u);
-            if (!(bf < __builtin_fmaf(sf, -kCertify, sf))) need |= 1u << (r * VEC + v);
-            cellv[r][v] = base + (slot / 3) * ncx + (slot % 3);
+            const unsigned best = umin3(lo[0][v], lo[1][v], lo[2][v]);
+            const unsigned second = min(umed3(lo[0][v], lo[1][v], lo[2][v]),
+                                        umin3(mid[0][v], mid[1][v], mid[2][v]));
+            if (second - best < kCertify) need |= 1u << (r * VEC + v);
+            cellv[r][v] = base + static_cast<int>((best >> 2) & 3u) * ncx + static_cast<int>(best & 3u);
         }
     }
     // near ties (a few pixels per frame): the reference argmin, after the
@@ -557,7 +571,7 @@ __global__ __launch_bounds__(kThreads, DIST == 0 ? 4 : 1) void assign_kernel(
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
             const int y = y0 + ty * ROWS + r;
-            const int base = (min(y, g.h - 1) / S - gy_lo - 1) * ncx + gx_rel;
+            const int base = rowbase[r];
 #pragma unroll
             for (int v = 0; v < VEC; ++v) {
                 if (!(need & (1u << (r * VEC + v)))) continue;
@@ -885,6 +899,7 @@ AssignImage assign_image(const Workspace& ws, int32_t w, int32_t h, const Grid& 
     a.counts = ws.counts;
     a.labels = ws.labels;
     a.sums = ws.sums;
+    a.by_S = make_divisor(g.S);
     a.tiles_x = 0;
     assign_tiles(variant, w, h, &a.tiles_x, nullptr);
     return a;

@@ -22,6 +22,27 @@ constexpr int kCenStride = 8;
 // Per-cluster accumulators: sum qL, qa, qb, x, y and the pixel count.
 constexpr int kSumStride = 6;
 
+// Exact quotient n / d of 0 <= n < 2^31 by a divisor fixed on the host:
+// floor(2n m / 2^(32 + shift)) with m = ceil(2^(31 + shift) / d) and
+// 2^shift >= d (m d exceeds 2^(31 + shift) by less than 2^shift, so the
+// quotient is exact).  An integer division by a kernel argument is some 30
+// dependent instructions, at the head of kernels that are bound by latency.
+struct Divisor {
+    uint32_t m;
+    int32_t shift;
+    __device__ __forceinline__ int quotient(int n) const {
+        return static_cast<int>(__umulhi(static_cast<unsigned>(n) << 1, m) >> shift);
+    }
+};
+inline Divisor make_divisor(int32_t d) {
+    Divisor r;
+    r.shift = 0;
+    while ((1ll << r.shift) < d) ++r.shift;
+    r.m = static_cast<uint32_t>(((1ull << (31 + r.shift)) + static_cast<uint64_t>(d) - 1) /
+                                static_cast<uint64_t>(d));
+    return r;
+}
+
 struct Grid {
     int32_t S, ns_c, ns_r, K;
     float w;      // m / S in FP32, the factor of d_xy in Eq. 1
@@ -87,6 +108,7 @@ struct AssignImage {
     int32_t* labels;   // N
     long long* sums;   // ring of 3 x K x kSumStride accumulators
     int tiles_x;       // workgroup tiles per row (for the launch's variant)
+    Divisor by_S;          // quotients by S
 };
 
 // Batch launches: workgroup b works on tile b - tile_first[i] of image
