@@ -38,6 +38,7 @@
 // its value), and clears sums[(t + 1) % 3] for the next launch.  The
 // workgroup holding a cell's first pixel owns that centre: it stores the new
 // centre and count and clears the next buffer.
+#include "assign_tile.h"
 #include "ccl_tile.h"
 #include "slic_internal.h"
 
@@ -45,110 +46,6 @@
 
 namespace slic {
 namespace {
-
-constexpr int kThreads = 256;
-constexpr unsigned kCertify = 160;  // distance of two keys
-
-// Reference Eq. 1 distance: the exact operation sequence of the definition.
-__device__ __forceinline__ float eq1_reference(float cl, float ca, float cb, float cx, float cy,
-                                               float l, float a, float b, float xf, float yf,
-                                               float wgt) {
-    const float dl = cl - l, da = ca - a, db = cb - b;
-    float s = dl * dl;
-    s = s + da * da;
-    s = s + db * db;
-    const float dlab = sqrtf(s);
-    const float dx = cx - xf, dy = cy - yf;
-    float t = dx * dx;
-    t = t + dy * dy;
-    const float dxy = sqrtf(t);
-    const float sp = wgt * dxy;
-    return dlab + sp;
-}
-
-// Fast Eq. 1 distance (fused multiply-adds, hardware square root); dy2 is
-// the squared vertical offset, shared by the pixels of a row.
-__device__ __forceinline__ float eq1_fast(float cl, float ca, float cb, float cx, float dy2,
-                                          float l, float a, float b, float xf, float wgt) {
-    const float dl = cl - l, da = ca - a, db = cb - b;
-    const float s = __builtin_fmaf(db, db, __builtin_fmaf(da, da, dl * dl));
-    const float dx = cx - xf;
-    const float t = __builtin_fmaf(dx, dx, dy2);
-    return __builtin_fmaf(wgt, __builtin_amdgcn_sqrtf(t), __builtin_amdgcn_sqrtf(s));
-}
-
-// Smallest and middle of three keys (the forms that compile to one
-// v_min3_u32 and one v_med3_u32).
-__device__ __forceinline__ unsigned umin3(unsigned a, unsigned b, unsigned c) {
-    return min(a, min(b, c));
-}
-__device__ __forceinline__ unsigned umed3(unsigned a, unsigned b, unsigned c) {
-    return max(min(a, b), min(max(a, b), c));
-}
-
-// Global (device) memory as a named address space: accesses through such
-// pointers compile to global rather than flat memory instructions (flat ones
-// also count against the LDS wait counter, so every LDS wait would wait for
-// them too).
-template <class T>
-using gmem = __attribute__((address_space(1))) T;
-
-template <class T>
-__device__ __forceinline__ gmem<T>* as_global(T* p) {
-    return (gmem<T>*)p;
-}
-
-// 16-byte global accesses (builtin vector types: HIP's float4 and int4 are
-// classes whose members assume generic pointers).
-typedef float vf4 __attribute__((ext_vector_type(4)));
-typedef int vi4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ float4 load_f4(gmem<const float>* p) {
-    const vf4 v = *reinterpret_cast<gmem<const vf4>*>(p);
-    return make_float4(v.x, v.y, v.z, v.w);
-}
-
-__device__ __forceinline__ void store_f4(gmem<float>* p, float4 v) {
-    *reinterpret_cast<gmem<vf4>*>(p) = vf4{v.x, v.y, v.z, v.w};
-}
-
-__device__ __forceinline__ void store_i4(gmem<int32_t>* p, int a, int b, int c, int d) {
-    *reinterpret_cast<gmem<vi4>*>(p) = vi4{a, b, c, d};
-}
-
-typedef float vf2 __attribute__((ext_vector_type(2)));
-typedef int vi2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ vf2 load_f2(gmem<const float>* p) {
-    return *reinterpret_cast<gmem<const vf2>*>(p);
-}
-
-__device__ __forceinline__ void store_i2(gmem<int32_t>* p, int a, int b) {
-    *reinterpret_cast<gmem<vi2>*>(p) = vi2{a, b};
-}
-
-// Reference argmin over the nine candidates of one pixel (near ties only).
-// A cell outside the grid is staged with an infinite colour distance and
-// every distance of a cell inside it is finite (the compactness bound), so
-// the strict test below never selects an outside cell; the pixel's own cell
-// (slot 4) is the starting choice.
-__device__ __forceinline__ int reference_slot(const float4* cen4, const float* ceny, int base,
-                                              int ncx, float l, float a, float b, float xf,
-                                              float yf, float wgt) {
-    float bref = __builtin_huge_valf();
-    int sref = 4;
-#pragma unroll 1
-    for (int c = 0; c < 9; ++c) {
-        const int li = base + (c / 3) * ncx + (c % 3);
-        const float4 q = cen4[li];
-        const float d = eq1_reference(q.x, q.y, q.z, q.w, ceny[li], l, a, b, xf, yf, wgt);
-        if (d < bref) {
-            bref = d;
-            sref = c;
-        }
-    }
-    return sref;
-}
 
 // A workgroup's image: from the kernel argument (one image) or, for a batch,
 // from the image table through the tile-to-image map.
@@ -166,53 +63,6 @@ __device__ __forceinline__ void resolve_image(const AssignImage& single, const A
         *bx = blockIdx.x;
         *by = blockIdx.y;
     }
-}
-
-// Shared-memory layout (dynamic): for every cell of the staged window
-// (the workgroup's cells plus a one-cell ring, out-of-grid cells included):
-//   float4 cen4[n] (L, a, b, x), float ceny[n], int kidx[n] (-1: none),
-//   u64 bins[4][n] (sum qL, sum qa, sum qb, packed x'|y'<<20|count<<40).
-__host__ __device__ inline size_t assign_lds_bytes(int ncells) {
-    return static_cast<size_t>(ncells) * (16 + 4 + 4 + 32) + 16;
-}
-
-// Launch shape of a variant: each thread owns VEC horizontally adjacent
-// pixels in each of ROWS consecutive rows.  VEC = 2 or 4 uses 8- or 16-byte
-// loads and evaluates each staged centre once for the VEC pixels, so it
-// needs them in one cell (S % VEC == 0) and aligned rows (width % VEC == 0).
-template <int VEC, int ROWS, int TX = (VEC == 4 ? 16 : 32)>
-struct Shape {
-    static constexpr int kTX = TX;  // threads per row
-    static constexpr int kTY = kThreads / kTX;
-    static constexpr int kTileW = kTX * VEC;
-    static constexpr int kTileH = kTY * ROWS;
-    static constexpr int kPx = VEC * ROWS;
-};
-
-__device__ __forceinline__ void add_bin(unsigned long long* bins, int ncells, int cell,
-                                        long long rl, long long ra, long long rb,
-                                        unsigned long long rxyc) {
-    atomicAdd(bins + cell, static_cast<unsigned long long>(rl));
-    atomicAdd(bins + ncells + cell, static_cast<unsigned long long>(ra));
-    atomicAdd(bins + 2 * ncells + cell, static_cast<unsigned long long>(rb));
-    atomicAdd(bins + 3 * ncells + cell, rxyc);
-}
-
-// The squared-sum distance of the SLIC paper the method builds on (an
-// option): d_lab^2 + w^2 d_xy^2 in FP32 in this order, no square roots, so
-// its argmin is taken exactly.
-__device__ __forceinline__ float dist_squared(float cl, float ca, float cb, float cx, float dy2,
-                                              float l, float a, float b, float xf, float wgt) {
-    const float dl = cl - l, da = ca - a, db = cb - b;
-    float s = dl * dl;
-    s = s + da * da;
-    s = s + db * db;
-    const float dx = cx - xf;
-    float t = dx * dx;
-    t = t + dy2;
-    const float w2 = wgt * wgt;
-    const float sp = w2 * t;
-    return s + sp;
 }
 
 // Launch modes: one image, one image with the convergence stop, a batch,
@@ -242,9 +92,12 @@ using LaunchShape =
 template <int VEC, int ROWS, int DIST, int MODE>
 __global__ __launch_bounds__(kThreads, DIST == 0 ? 4 : 1) void assign_kernel(
     AssignImage single, AssignTileMap map, long long t, Converge cv, AssignCcl cc,
-    int store_labels) {
+    int store_labels, int copies) {
     using Sh = LaunchShape<VEC, ROWS, MODE>;
     constexpr bool kConv = MODE == kModeConverge;
+    // the last launch before the connectivity clean-up only stores the
+    // labels: no update follows it
+    constexpr bool kSums = MODE != kModeFinalCcl;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ unsigned long long s_shift;
     if constexpr (kConv) {  // convergence stop: every workgroup takes the same decision
@@ -367,7 +220,6 @@ __global__ __launch_bounds__(kThreads, DIST == 0 ? 4 : 1) void assign_kernel(
     auto stage_finish = [&](int i, const Slot& st) {
         if (i >= ncells) return;
         const int cx = st.cx, cy = st.cy;
-        for (int j = 0; j < 4; ++j) bins[j * ncells + i] = 0ull;
         if (st.k < 0) {
             // no centre here: an infinite colour distance never wins
             cen4[i] = make_float4(__builtin_huge_valf(), 0.0f, 0.0f, 0.0f);
@@ -450,8 +302,7 @@ __global__ __launch_bounds__(kThreads, DIST == 0 ? 4 : 1) void assign_kernel(
         for (int i = threadIdx.x; i < ncells; i += kThreads) {
             const int row = static_cast<int>((static_cast<float>(i) + 0.5f) * inv_ncx);
             const int cx = gx_lo + (i - row * ncx), cy = gy_lo + row;
-            for (int j = 0; j < 4; ++j) bins[j * ncells + i] = 0ull;
-            if (cx < 0 || cy < 0 || cx >= g.ns_c || cy >= g.ns_r) {
+                if (cx < 0 || cy < 0 || cx >= g.ns_c || cy >= g.ns_r) {
                 // no centre here: an infinite colour distance never wins
                 cen4[i] = make_float4(__builtin_huge_valf(), 0.0f, 0.0f, 0.0f);
                 ceny[i] = 0.0f;
@@ -482,6 +333,9 @@ __global__ __launch_bounds__(kThreads, DIST == 0 ? 4 : 1) void assign_kernel(
             ceny[i] = vy;
         }
     }
+    if constexpr (kSums) {
+        for (int j = threadIdx.x; j < copies * bin_stride(ncells); j += kThreads) bins[j] = 0ull;
+    }
     __syncthreads();
     if (my_shift) atomicAdd(&s_shift, static_cast<unsigned long long>(my_shift));
 
@@ -491,170 +345,54 @@ __global__ __launch_bounds__(kThreads, DIST == 0 ? 4 : 1) void assign_kernel(
     // tile's first cell, so every staged-window index stays in range)
     const int gx_rel = g.by_S.quotient(col_ok ? x : x0) - gx_lo - 1;
     int cellv[ROWS][VEC];
-    int rowbase[ROWS];
-    unsigned need = 0;  // pixels whose fast argmin is not certified: bit r * VEC + v
-#pragma unroll
-    for (int r = 0; r < ROWS; ++r) {
-        const int y = y0 + ty * ROWS + r;
-        const float yf = static_cast<float>(y);
-        const int base = (g.by_S.quotient(min(y, g.h - 1)) - gy_lo - 1) * ncx + gx_rel;
-        rowbase[r] = base;
-        if constexpr (DIST == 1) {
-            // exact: (distance bits, slot) as one 64-bit key, lowest slot on ties
-            unsigned long long bk[VEC];
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) bk[v] = ~0ull;
-#pragma unroll
-            for (int c = 0; c < 9; ++c) {
-                const int li = base + (c / 3) * ncx + (c % 3);
-                const float4 q = cen4[li];
-                const float dy = ceny[li] - yf;
-                const float dy2 = dy * dy;
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    const float d = dist_squared(q.x, q.y, q.z, q.w, dy2, pl[r][v], pa[r][v],
-                                                 pb[r][v], static_cast<float>(x + v), g.wgt);
-                    const unsigned long long key =
-                        (static_cast<unsigned long long>(__float_as_uint(d)) << 4) |
-                        static_cast<unsigned long long>(c);
-                    bk[v] = key < bk[v] ? key : bk[v];
-                }
-            }
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                // an out-of-grid cell (infinite distance) can only come first
-                // when no distance is finite; the own cell is then taken
-                int slot = static_cast<int>(bk[v] & 15ull);
-                const int cell = base + (slot / 3) * ncx + (slot % 3);
-                cellv[r][v] = kidx[cell] < 0 ? base + ncx + 1 : cell;
-            }
-            continue;
-        }
-        // the keys of one row of candidates at a time: smallest and middle of
-        // three (one instruction each), then of the three rows
-        unsigned lo[3][VEC], mid[3][VEC];
-#pragma unroll
-        for (int cr = 0; cr < 3; ++cr) {
-            unsigned key[3][VEC];
-#pragma unroll
-            for (int cc = 0; cc < 3; ++cc) {
-                const int li = base + cr * ncx + cc;
-                const float4 q = cen4[li];
-                const float dy = ceny[li] - yf;
-                const float dy2 = dy * dy;
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    const float d = eq1_fast(q.x, q.y, q.z, q.w, dy2, pl[r][v], pa[r][v], pb[r][v],
-                                             static_cast<float>(x + v), g.wgt);
-                    key[cc][v] = (__float_as_uint(d) & ~15u) | static_cast<unsigned>(4 * cr + cc);
-                }
-            }
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                lo[cr][v] = umin3(key[0][v], key[1][v], key[2][v]);
-                mid[cr][v] = umed3(key[0][v], key[1][v], key[2][v]);
-            }
-        }
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) {
-            const unsigned best = umin3(lo[0][v], lo[1][v], lo[2][v]);
-            const unsigned second = min(umed3(lo[0][v], lo[1][v], lo[2][v]),
-                                        umin3(mid[0][v], mid[1][v], mid[2][v]));
-            if (second - best < kCertify) need |= 1u << (r * VEC + v);
-            cellv[r][v] = base + static_cast<int>((best >> 2) & 3u) * ncx + static_cast<int>(best & 3u);
-        }
-    }
-    // near ties (a few pixels per frame): the reference argmin, after the
-    // fast pass, whose keys are then dead, and inline (a call would pin the
-    // fast pass's live values to the callee-saved registers)
-    if (need) {
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-            const int y = y0 + ty * ROWS + r;
-            const int base = rowbase[r];
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                if (!(need & (1u << (r * VEC + v)))) continue;
-                const int slot = reference_slot(cen4, ceny, base, ncx, pl[r][v], pa[r][v],
-                                                pb[r][v], static_cast<float>(x + v),
-                                                static_cast<float>(y), g.wgt);
-                cellv[r][v] = base + (slot / 3) * ncx + (slot % 3);
-            }
-        }
-    }
+    find_cells<VEC, ROWS, DIST>(cen4, ceny, kidx, ncx, gx_rel, gy_lo, g, x, y0 + ty * ROWS, pl, pa, pb,
+                                cellv);
 
-    // ---- labels, then runs of equal cells into the LDS bins (the last
-    // launch before the connectivity clean-up only stores the labels: no
-    // update follows it)
-    constexpr bool kSums = MODE != kModeFinalCcl;
-    const float scale = static_cast<float>(1 << kQShift);
-    int run_cell = -1;
-    int rl = 0, ra = 0, rb = 0;
-    unsigned long long rxyc = 0;
+    // ---- labels, then runs of equal cells into the LDS bins
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
         const int y = y0 + ty * ROWS + r;
-        if (!col_ok || y >= g.h) continue;
+        if (!col_ok || y >= g.h || !store_labels) continue;
         const size_t pi = static_cast<size_t>(y) * g.w + x;
-        if (store_labels) {
-            if constexpr (VEC == 4) {
-                store_i4(labels + pi, kidx[cellv[r][0]], kidx[cellv[r][1]], kidx[cellv[r][2]],
-                         kidx[cellv[r][3]]);
-            } else if constexpr (VEC == 2) {
-                store_i2(labels + pi, kidx[cellv[r][0]], kidx[cellv[r][1]]);
-            } else {
-                labels[pi] = kidx[cellv[r][0]];
-            }
-        }
-        if constexpr (!kSums) continue;
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) {
-            const int cell = cellv[r][v];
-            const int ql = static_cast<int>(rintf(pl[r][v] * scale));
-            const int qa = static_cast<int>(rintf(pa[r][v] * scale));
-            const int qb = static_cast<int>(rintf(pb[r][v] * scale));
-            const unsigned long long xyc = static_cast<unsigned long long>(x + v - x0) |
-                                           (static_cast<unsigned long long>(y - y0) << 20) |
-                                           (1ull << 40);
-            if (cell != run_cell) {
-                if (run_cell >= 0) add_bin(bins, ncells, run_cell, rl, ra, rb, rxyc);
-                run_cell = cell;
-                rl = ql;
-                ra = qa;
-                rb = qb;
-                rxyc = xyc;
-            } else {
-                rl += ql;
-                ra += qa;
-                rb += qb;
-                rxyc += xyc;
-            }
+        if constexpr (VEC == 4) {
+            store_i4(labels + pi, kidx[cellv[r][0]], kidx[cellv[r][1]], kidx[cellv[r][2]],
+                     kidx[cellv[r][3]]);
+        } else if constexpr (VEC == 2) {
+            store_i2(labels + pi, kidx[cellv[r][0]], kidx[cellv[r][1]]);
+        } else {
+            labels[pi] = kidx[cellv[r][0]];
         }
     }
     if constexpr (kSums) {
-        if (run_cell >= 0) add_bin(bins, ncells, run_cell, rl, ra, rb, rxyc);
+        unsigned long long* const mine = bins + (threadIdx.x & (copies - 1)) * bin_stride(ncells);
+        accumulate<VEC, ROWS>(mine, ncells, cellv, pl, pa, pb, tx * VEC, ty * ROWS,
+                              col_ok ? g.h - (y0 + ty * ROWS) : 0);
         __syncthreads();
         if constexpr (kConv) {
             if (threadIdx.x == 0 && s_shift)
                 atomicAdd(reinterpret_cast<unsigned long long*>(cv.ctl + t % 3), s_shift);
         }
 
-        // ---- add the workgroup's bins to the global sums
-        for (int i = threadIdx.x; i < ncells; i += kThreads) {
-            const unsigned long long p = bins[3 * ncells + i];
-            const long long n = static_cast<long long>(p >> 40);
-            if (n == 0) continue;
-            const long long sx = static_cast<long long>(p & 0xFFFFFull) + n * x0;
-            const long long sy = static_cast<long long>((p >> 20) & 0xFFFFFull) + n * y0;
+        // ---- add the workgroup's bins to the global sums, one thread per word
+        // of a cell
+        for (int i = threadIdx.x; i < 4 * ncells; i += kThreads) {
+            const int comp = (i >= ncells) + (i >= 2 * ncells) + (i >= 3 * ncells);
+            unsigned long long p = 0;
+            for (int c = 0; c < copies; ++c) p += bins[c * bin_stride(ncells) + i];
+            if (p == 0) continue;
             gmem<unsigned long long>* s = reinterpret_cast<gmem<unsigned long long>*>(
-                sums_acc + static_cast<size_t>(kidx[i]) * kSumStride);
-            const unsigned long long add[kSumStride] = {
-                bins[i], bins[ncells + i], bins[2 * ncells + i],
-                static_cast<unsigned long long>(sx), static_cast<unsigned long long>(sy),
-                static_cast<unsigned long long>(n)};
-#pragma unroll
-            for (int j = 0; j < kSumStride; ++j)
-                __hip_atomic_fetch_add(s + j, add[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                sums_acc + static_cast<size_t>(kidx[i - comp * ncells]) * kSumStride);
+            auto add = [&](int j, unsigned long long v) {
+                __hip_atomic_fetch_add(s + j, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            };
+            if (comp < 3) {
+                add(comp, p);
+            } else {
+                const long long n = static_cast<long long>(p >> 48);
+                add(3, static_cast<unsigned long long>(static_cast<long long>(p & 0xFFFFFFull) + n * x0));
+                add(4, static_cast<unsigned long long>(static_cast<long long>((p >> 24) & 0xFFFFFFull) + n * y0));
+                add(5, static_cast<unsigned long long>(n));
+            }
         }
     }
 
@@ -757,10 +495,16 @@ __global__ __launch_bounds__(256) void import_centres_kernel(int K, const float*
 }
 
 template <int VEC, int ROWS>
-size_t variant_lds(int S) {
+int variant_cells(int S) {
     using Sh = Shape<VEC, ROWS>;
     // window of cells over any tile: at most (tile - 1)/S + 4 per side
-    return assign_lds_bytes(((Sh::kTileW - 1) / S + 4) * ((Sh::kTileH - 1) / S + 4));
+    return ((Sh::kTileW - 1) / S + 4) * ((Sh::kTileH - 1) / S + 4);
+}
+
+template <int VEC, int ROWS>
+size_t variant_lds(int S) {
+    const int n = variant_cells<VEC, ROWS>(S);
+    return assign_lds_bytes(n, bin_copies(n));
 }
 
 template <int VEC, int ROWS, int DIST>
@@ -776,15 +520,16 @@ hipError_t launch_variant(const AssignImage& a, const AssignTileMap& map, int to
     }
     KernelTimer timer("assign", s);
     const size_t lds = variant_lds<VEC, ROWS>(min_S);
+    const int copies = bin_copies(variant_cells<VEC, ROWS>(min_S));
     if (map.images) {
         assign_kernel<VEC, ROWS, DIST, kModeBatch><<<grid, kThreads, lds, s>>>(a, map, t, cv, {},
-                                                                              store);
+                                                                              store, copies);
     } else if (cv.ctl) {
         assign_kernel<VEC, ROWS, DIST, kModeConverge><<<grid, kThreads, lds, s>>>(a, map, t, cv,
-                                                                                 {}, store);
+                                                                                 {}, store, copies);
     } else {
         assign_kernel<VEC, ROWS, DIST, kModeSingle><<<grid, kThreads, lds, s>>>(a, map, t, cv, {},
-                                                                               store);
+                                                                               store, copies);
     }
     return hipGetLastError();
 }
@@ -796,7 +541,7 @@ hipError_t launch_variant(const AssignImage& a, const AssignTileMap& map, int to
 template <int VEC, int ROWS>
 size_t final_ccl_lds(int S) {
     using Sh = LaunchShape<VEC, ROWS, kModeFinalCcl>;
-    return assign_lds_bytes(((Sh::kTileW - 1) / S + 4) * ((Sh::kTileH - 1) / S + 4));
+    return assign_lds_bytes(((Sh::kTileW - 1) / S + 4) * ((Sh::kTileH - 1) / S + 4), 1);
 }
 
 template <int VEC, int ROWS, int DIST>
@@ -808,7 +553,7 @@ hipError_t launch_final_ccl(const AssignImage& a, long long t, const AssignCcl& 
     const Converge off{nullptr, 0, 0};
     KernelTimer timer("assign", s);
     assign_kernel<VEC, ROWS, DIST, kModeFinalCcl><<<grid, kThreads, final_ccl_lds<VEC, ROWS>(S),
-                                                     s>>>(a, none, t, off, cc, 1);
+                                                     s>>>(a, none, t, off, cc, 1, 1);
     return hipGetLastError();
 }
 
