@@ -202,8 +202,20 @@ hipError_t enqueue_init(slic_ctx* c, const uint8_t* rgb, bool* ccl = nullptr, bo
 // n rounds of (update, associate): each association launch also completes
 // the previous launch's centre update (ccl: as in associate, for the last
 // of them; untouched when n is 0).  Only the last launch writes the labels.
-hipError_t enqueue_iterations(slic_ctx* c, int32_t n, bool* ccl = nullptr) {
-    for (int32_t i = 0; i < n; ++i) {
+// Where the frame suits it, one launch runs all rounds (all but the last with
+// *ccl, whose launch has tiles of its own).  cleared: as in launch_rounds.
+hipError_t enqueue_iterations(slic_ctx* c, int32_t n, bool* ccl = nullptr, bool cleared = false) {
+    const bool tail = ccl && *ccl;
+    const int32_t together = n - (tail ? 1 : 0);
+    int32_t i = 0;
+    if (rounds_supported(c->ws, c->p.width, c->p.height, c->g, c->variant, together)) {
+        const hipError_t e = launch_rounds(c->ws, c->p.width, c->p.height, c->g, c->t, together,
+                                           c->variant, !tail, true, cleared, c->stream);
+        if (e != hipSuccess) return e;
+        c->t += together;
+        i = together;
+    }
+    for (; i < n; ++i) {
         hipError_t e = associate(c, i == n - 1 ? ccl : nullptr, i == n - 1);
         if (e != hipSuccess) return e;
         ++c->t;
@@ -487,9 +499,24 @@ int enqueue_segment(const slic_params* p, const uint8_t* d_rgb, int32_t n_iters,
     c.ws.labels = d_labels;  // associate straight into the caller's buffer
     // the last association also finds the tile-local components, if it can
     bool local_done = enforce != 0;
-    if (enqueue_init(&c, d_rgb, n_iters == 0 ? &local_done : nullptr, n_iters == 0) != hipSuccess)
-        return SLIC_EHIP;
-    if (enqueue_iterations(&c, n_iters, &local_done) != hipSuccess) return SLIC_EHIP;
+    // all associations (all but that one) in one launch, where the frame suits it
+    const int32_t together = enforce ? n_iters : n_iters + 1;
+    if (rounds_supported(c.ws, p->width, p->height, c.g, c.variant, together)) {
+        size_t words = 0;
+        uint32_t* const clear = rounds_clear(c.ws, p->width, p->height, c.g, c.variant, &words);
+        if (launch_lab_seed(d_rgb, p->width, p->height, p->pitch, p->channels, c.ws, c.g,
+                            (p->flags & SLIC_PERTURB_SEEDS) ? 1 : 0, c.stream, clear, words) !=
+                hipSuccess ||
+            launch_rounds(c.ws, p->width, p->height, c.g, 0, together, c.variant, !enforce,
+                          enforce != 0, true, c.stream) != hipSuccess)
+            return SLIC_EHIP;
+        c.t = together;
+        if (enforce && associate(&c, &local_done, true) != hipSuccess) return SLIC_EHIP;
+    } else {
+        if (enqueue_init(&c, d_rgb, n_iters == 0 ? &local_done : nullptr, n_iters == 0) != hipSuccess)
+            return SLIC_EHIP;
+        if (enqueue_iterations(&c, n_iters, &local_done) != hipSuccess) return SLIC_EHIP;
+    }
     if (d_energy &&
         launch_energy(c.ws, p->width, p->height, c.g, d_energy, c.stream) != hipSuccess)
         return SLIC_EHIP;
@@ -762,10 +789,13 @@ namespace {
 // whether the decoded labels are written; rounds that follow at once make
 // them dead).
 hipError_t enqueue_warm_init(slic_ctx* c, const uint8_t* rgb, const void* d_net,
-                             bool store = true) {
+                             bool store = true, bool clear = false) {
     const slic_params& p = c->p;
+    size_t words = 0;
+    uint32_t* const to_clear =
+        clear ? rounds_clear(c->ws, p.width, p.height, c->g, c->variant, &words) : nullptr;
     hipError_t e = launch_lab_seed(rgb, p.width, p.height, p.pitch, p.channels, c->ws, c->g,
-                                   (p.flags & SLIC_PERTURB_SEEDS) ? 1 : 0, c->stream);
+                                   (p.flags & SLIC_PERTURB_SEEDS) ? 1 : 0, c->stream, to_clear, words);
     if (e != hipSuccess) return e;
     c->t = 0;
     e = launch_warm_start(c->ws, p.width, p.height, c->g, d_net, c->stream, store);
@@ -826,10 +856,12 @@ int slic_warm_segment(const slic_params* p, const uint8_t* d_rgb, const void* d_
     slic_ctx c;
     bind(&c, p, d_ws, hip_stream);
     c.ws.labels = d_labels;
-    if (enqueue_warm_init(&c, d_rgb, d_net, n_iters == 0) != hipSuccess) return SLIC_EHIP;
     // with rounds, the last association also finds the tile-local components
     bool local_done = enforce != 0 && n_iters > 0;
-    if (enqueue_iterations(&c, n_iters, &local_done) != hipSuccess) return SLIC_EHIP;
+    const bool together = rounds_supported(c.ws, p->width, p->height, c.g, c.variant,
+                                           n_iters - (local_done ? 1 : 0));
+    if (enqueue_warm_init(&c, d_rgb, d_net, n_iters == 0, together) != hipSuccess) return SLIC_EHIP;
+    if (enqueue_iterations(&c, n_iters, &local_done, together) != hipSuccess) return SLIC_EHIP;
     if (d_energy &&
         launch_energy(c.ws, p->width, p->height, c.g, d_energy, c.stream) != hipSuccess)
         return SLIC_EHIP;

@@ -208,6 +208,12 @@ __global__ __launch_bounds__(NT) void lab_seed_kernel(LabSeedImage single, LabSe
     __shared__ float sL[kSW * kSH], sA[kSW * kSH], sB[kSW * kSH];
     __shared__ float grad[NT];
     if (threadIdx.x < 256) lin[threadIdx.x] = tab.lin[threadIdx.x];
+    if constexpr (!kBatch) {
+        const unsigned step = gridDim.x * gridDim.y * NT;
+        for (unsigned i = (blockIdx.y * gridDim.x + blockIdx.x) * NT + threadIdx.x;
+             i < single.n_clear; i += step)
+            single.clear[i] = make_uint4(0u, 0u, 0u, 0u);
+    }
     LabSeedImage g;
     int bx, by;
     if constexpr (kBatch) {  // batch: this workgroup's image from the tile map
@@ -347,6 +353,8 @@ LabSeedImage lab_seed_image(const uint8_t* rgb, int32_t w, int32_t h, int32_t pi
     a.counts = ws.counts;
     a.sums = ws.sums;
     a.tiles_x = (w + kTW - 1) / kTW;
+    a.clear = nullptr;
+    a.n_clear = 0;
     return a;
 }
 
@@ -365,8 +373,10 @@ int compute_units() {
 
 hipError_t launch_lab_seed(const uint8_t* rgb, int32_t w, int32_t h, int32_t pitch,
                            int32_t channels, const Workspace& ws, const Grid& grid, int perturb,
-                           hipStream_t s) {
-    const LabSeedImage a = lab_seed_image(rgb, w, h, pitch, channels, ws, grid, perturb);
+                           hipStream_t s, uint32_t* clear, size_t n_clear) {
+    LabSeedImage a = lab_seed_image(rgb, w, h, pitch, channels, ws, grid, perturb);
+    a.clear = reinterpret_cast<uint4*>(clear);
+    a.n_clear = clear ? static_cast<uint32_t>(n_clear / 4) : 0;  // (words: a multiple of 4)
     const LabSeedTileMap none{nullptr, nullptr, nullptr};
     KernelTimer t("lab_seed", s);
     const int cus = compute_units();

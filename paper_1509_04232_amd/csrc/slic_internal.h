@@ -81,6 +81,8 @@ struct LabSeedImage {
     int32_t* counts;
     long long* sums;  // first accumulator buffer
     int tiles_x;      // conversion tiles per row
+    uint4* clear;  // memory to zero for a launch that follows (16-byte units)
+    uint32_t n_clear;
 };
 struct LabSeedTileMap {
     const LabSeedImage* images;
@@ -89,7 +91,9 @@ struct LabSeedTileMap {
 };
 hipError_t launch_lab_seed(const uint8_t* rgb, int32_t w, int32_t h, int32_t pitch,
                            int32_t channels, const Workspace& ws, const Grid& grid, int perturb,
-                           hipStream_t s);
+                           hipStream_t s, uint32_t* clear = nullptr, size_t n_clear = 0);
+// Compute units of the current device.
+int compute_units();
 hipError_t launch_lab_seed_batch(const LabSeedTileMap& map, int total_tiles, hipStream_t s);
 LabSeedImage lab_seed_image(const uint8_t* rgb, int32_t w, int32_t h, int32_t pitch,
                             int32_t channels, const Workspace& ws, const Grid& grid, int perturb);
@@ -150,6 +154,20 @@ hipError_t launch_assign(const Workspace& ws, int32_t w, int32_t h, const Grid& 
 bool assign_final_ccl_supported(int32_t w, int32_t h, int32_t S);
 hipError_t launch_assign_final_ccl(const Workspace& ws, int32_t w, int32_t h, const Grid& g,
                                   int64_t t, hipStream_t s);
+// Associations t0 .. t0 + n - 1 in one launch (rounds.hip), with the labels
+// of the last one (store_last) and its sums in the ring (sums_last: another
+// association follows).  Only where rounds_supported.  The words that
+// rounds_clear names must be zero: `cleared` says that an earlier launch of
+// the stream has done so, else the call does.
+// census_ticks: how long a workgroup waits for the others to start, in
+// 10 ns (negative: the built-in time).
+constexpr int kMinRounds = 2;
+bool rounds_supported(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int variant, int n);
+uint32_t* rounds_clear(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int variant,
+                       size_t* words);
+hipError_t launch_rounds(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int64_t t0, int n,
+                         int variant, bool store_last, bool sums_last, bool cleared, hipStream_t s,
+                         int census_ticks = -1);
 hipError_t launch_assign_batch(const AssignTileMap& map, int total_tiles, int min_S, int64_t t,
                                int variant, int dist, hipStream_t s, bool store_labels = true);
 AssignImage assign_image(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int variant);

@@ -1,0 +1,121 @@
+"""All rounds of a frame in one launch (csrc/rounds.hip) against the oracle,
+bit for bit: tiles at the image's edges, cells that meet few and many tiles,
+both distances, rounds continued by later calls, a captured segmentation
+replayed beside other work, and frames that share the chip with other
+streams' kernels (so that not every workgroup of the launch starts at
+once)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def slic():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    import paper_1509_04232_amd as slic
+    return slic
+
+
+def _img(w, h, seed):
+    return synth.voronoi_image(seed, w, h, max(2, w * h // 900), 8.0)
+
+
+def _gpu(img):
+    return torch.from_numpy(np.ascontiguousarray(img).reshape(-1)).cuda()
+
+
+@pytest.mark.parametrize("squared", [False, True])
+@pytest.mark.parametrize("w,h,S", [
+    (64, 48, 4), (65, 33, 5), (129, 97, 8), (320, 240, 16), (333, 251, 27), (640, 31, 16),
+    (97, 640, 32), (512, 400, 85), (512, 400, 86), (1030, 1027, 8), (1500, 1400, 12),
+])
+def test_split_rounds_match_oracle(slic, squared, w, h, S):
+    img = _img(w, h, w + h + S)
+    dist = oracle.DIST_SQUARED if squared else oracle.DIST_EQ1
+    p = slic.Params(w, h, S=S, m=10.0, squared_distance=squared)
+    ctx = slic.Context(p, _gpu(img))
+    done = 0
+    for n in (3, 1, 4):
+        ctx.iterate(n)
+        done += n
+        want = oracle.segment(img, S, 10.0, done, True, False, 0, oracle.COLOR_LAB, dist)
+        lb, (cen, cnt) = ctx.labels(), ctx.centres()
+        torch.cuda.synchronize()
+        assert np.array_equal(lb.cpu().numpy(), want["labels"]), done
+        assert np.array_equal(cen.cpu().numpy(), want["centres"]), done
+        assert np.array_equal(cnt.cpu().numpy(), want["counts"]), done
+    ctx.close()
+
+
+def test_empty_clusters_keep_their_centres(slic):
+    # two flat halves at m = 0: most centres lose all their pixels
+    w, h, S = 192, 128, 8
+    img = np.zeros((h, w, 3), np.uint8)
+    img[:, w // 2:] = (200, 30, 90)
+    want = oracle.segment(img, S, 0.0, 6, False, False)
+    p = slic.Params(w, h, S=S, m=0.0, perturb=False)
+    out = slic.segment(_gpu(img), p, 6, want_centres=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(out["labels"].cpu().numpy(), want["labels"])
+    assert np.array_equal(out["centres"].cpu().numpy(), want["centres"])
+
+
+def test_captured_segmentation_replayed(slic):
+    from paper_1509_04232_amd import _abi
+    w, h, S = 320, 200, 16
+    imgs = [_img(w, h, s) for s in (1, 2, 3)]
+    want = [oracle.segment(i, S, 10.0, 5, True, True) for i in imgs]
+    p = slic.Params(w, h, S=S, m=10.0)
+    cp = p.c()
+    rgb = _gpu(imgs[0]).clone()
+    ws = slic.workspace_for(p)
+    labels = torch.empty((h, w), dtype=torch.int32, device="cuda")
+
+    def segment(stream):
+        _abi.slic_segment(cp, rgb.data_ptr(), 5, 1, labels.data_ptr(), None, None, None,
+                          stream.cuda_stream, ws.data_ptr(), ws.numel())
+
+    segment(torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        segment(torch.cuda.current_stream())
+    for k in (1, 2, 0, 1):
+        rgb.copy_(_gpu(imgs[k]))
+        other = torch.randn(512, 512, device="cuda")
+        (other @ other).sum()
+        labels.fill_(-1)
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(labels.cpu().numpy(), want[k]["seg_labels"])
+
+
+def test_frames_beside_other_kernels(slic):
+    w, h, S = 640, 480, 16
+    imgs = [_img(w, h, s) for s in (11, 12)]
+    want = [oracle.segment(i, S, 10.0, 6, True, False) for i in imgs]
+    p = slic.Params(w, h, S=S, m=10.0)
+    rgb = [_gpu(i) for i in imgs]
+    ws = [slic.workspace_for(p) for _ in imgs]
+    big = torch.randn(4096, 4096, device="cuda")
+    streams = [torch.cuda.Stream() for _ in imgs]
+    load = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    outs = []
+    for _ in range(4):
+        with torch.cuda.stream(load):
+            for _ in range(3):
+                big @ big
+        for i, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                outs.append((i, slic.segment(rgb[i], p, 6, workspace=ws[i])["labels"]))
+    torch.cuda.synchronize()
+    for i, lb in outs:
+        assert np.array_equal(lb.cpu().numpy(), want[i]["labels"])
