@@ -208,9 +208,10 @@ hipError_t enqueue_iterations(slic_ctx* c, int32_t n, bool* ccl = nullptr, bool 
     const bool tail = ccl && *ccl;
     const int32_t together = n - (tail ? 1 : 0);
     int32_t i = 0;
-    if (rounds_supported(c->ws, c->p.width, c->p.height, c->g, c->variant, together)) {
+    const int tiles = rounds_variant(c->ws, c->p.width, c->p.height, c->g, c->variant, together);
+    if (tiles) {
         const hipError_t e = launch_rounds(c->ws, c->p.width, c->p.height, c->g, c->t, together,
-                                           c->variant, !tail, true, cleared, c->stream);
+                                           tiles, !tail, true, cleared, c->stream);
         if (e != hipSuccess) return e;
         c->t += together;
         i = together;
@@ -501,13 +502,14 @@ int enqueue_segment(const slic_params* p, const uint8_t* d_rgb, int32_t n_iters,
     bool local_done = enforce != 0;
     // all associations (all but that one) in one launch, where the frame suits it
     const int32_t together = enforce ? n_iters : n_iters + 1;
-    if (rounds_supported(c.ws, p->width, p->height, c.g, c.variant, together)) {
+    const int tiles = rounds_variant(c.ws, p->width, p->height, c.g, c.variant, together);
+    if (tiles) {
         size_t words = 0;
-        uint32_t* const clear = rounds_clear(c.ws, p->width, p->height, c.g, c.variant, &words);
+        uint32_t* const clear = rounds_clear(c.ws, p->width, p->height, c.g, tiles, &words);
         if (launch_lab_seed(d_rgb, p->width, p->height, p->pitch, p->channels, c.ws, c.g,
                             (p->flags & SLIC_PERTURB_SEEDS) ? 1 : 0, c.stream, clear, words) !=
                 hipSuccess ||
-            launch_rounds(c.ws, p->width, p->height, c.g, 0, together, c.variant, !enforce,
+            launch_rounds(c.ws, p->width, p->height, c.g, 0, together, tiles, !enforce,
                           enforce != 0, true, c.stream) != hipSuccess)
             return SLIC_EHIP;
         c.t = together;
@@ -789,11 +791,11 @@ namespace {
 // whether the decoded labels are written; rounds that follow at once make
 // them dead).
 hipError_t enqueue_warm_init(slic_ctx* c, const uint8_t* rgb, const void* d_net,
-                             bool store = true, bool clear = false) {
+                             bool store = true, int tiles = 0) {
     const slic_params& p = c->p;
     size_t words = 0;
     uint32_t* const to_clear =
-        clear ? rounds_clear(c->ws, p.width, p.height, c->g, c->variant, &words) : nullptr;
+        tiles ? rounds_clear(c->ws, p.width, p.height, c->g, tiles, &words) : nullptr;
     hipError_t e = launch_lab_seed(rgb, p.width, p.height, p.pitch, p.channels, c->ws, c->g,
                                    (p.flags & SLIC_PERTURB_SEEDS) ? 1 : 0, c->stream, to_clear, words);
     if (e != hipSuccess) return e;
@@ -858,10 +860,10 @@ int slic_warm_segment(const slic_params* p, const uint8_t* d_rgb, const void* d_
     c.ws.labels = d_labels;
     // with rounds, the last association also finds the tile-local components
     bool local_done = enforce != 0 && n_iters > 0;
-    const bool together = rounds_supported(c.ws, p->width, p->height, c.g, c.variant,
-                                           n_iters - (local_done ? 1 : 0));
-    if (enqueue_warm_init(&c, d_rgb, d_net, n_iters == 0, together) != hipSuccess) return SLIC_EHIP;
-    if (enqueue_iterations(&c, n_iters, &local_done, together) != hipSuccess) return SLIC_EHIP;
+    const int tiles = rounds_variant(c.ws, p->width, p->height, c.g, c.variant,
+                                     n_iters - (local_done ? 1 : 0));
+    if (enqueue_warm_init(&c, d_rgb, d_net, n_iters == 0, tiles) != hipSuccess) return SLIC_EHIP;
+    if (enqueue_iterations(&c, n_iters, &local_done, tiles != 0) != hipSuccess) return SLIC_EHIP;
     if (d_energy &&
         launch_energy(c.ws, p->width, p->height, c.g, d_energy, c.stream) != hipSuccess)
         return SLIC_EHIP;

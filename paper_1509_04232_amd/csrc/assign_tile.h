@@ -31,17 +31,6 @@ __device__ __forceinline__ float eq1_reference(float cl, float ca, float cb, flo
     return dlab + sp;
 }
 
-// Fast Eq. 1 distance (fused multiply-adds, hardware square root); dy2 is
-// the squared vertical offset, shared by the pixels of a row.
-__device__ __forceinline__ float eq1_fast(float cl, float ca, float cb, float cx, float dy2,
-                                          float l, float a, float b, float xf, float wgt) {
-    const float dl = cl - l, da = ca - a, db = cb - b;
-    const float s = __builtin_fmaf(db, db, __builtin_fmaf(da, da, dl * dl));
-    const float dx = cx - xf;
-    const float t = __builtin_fmaf(dx, dx, dy2);
-    return __builtin_fmaf(wgt, __builtin_amdgcn_sqrtf(t), __builtin_amdgcn_sqrtf(s));
-}
-
 // Smallest and middle of three keys (the forms that compile to one
 // v_min3_u32 and one v_med3_u32).
 __device__ __forceinline__ unsigned umin3(unsigned a, unsigned b, unsigned c) {
@@ -176,6 +165,66 @@ __device__ __forceinline__ float dist_squared(float cl, float ca, float cb, floa
     return s + sp;
 }
 
+// Selection among the nine candidates of NR rows of VEC pixels, all in the
+// cells of window entry `base` (its left upper candidate): the winners' window
+// cells, and where the fast values do not certify the choice.  A candidate is loaded once for all the pixels, its
+// horizontal offsets are shared by the rows and its vertical ones by the
+// columns.
+template <int VEC, int NR>
+__device__ __forceinline__ void find_eq1(const float4* cen4, const float* ceny, int ncx, int base,
+                                         float wgt, int x, int yb, const float (*pl)[VEC],
+                                         const float (*pa)[VEC], const float (*pb)[VEC],
+                                         bool (*near)[VEC], int (*cellv)[VEC]) {
+    // the keys of one row of candidates at a time: smallest and middle of
+    // three (one instruction each), then of the three rows
+    unsigned lo[3][NR][VEC], mid[3][NR][VEC];
+#pragma unroll
+    for (int cr = 0; cr < 3; ++cr) {
+        unsigned key[3][NR][VEC];
+#pragma unroll
+        for (int cc = 0; cc < 3; ++cc) {
+            const int li = base + cr * ncx + cc;
+            const float4 q = cen4[li];
+            const float qy = ceny[li];
+            float dx[VEC];
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) dx[v] = q.w - static_cast<float>(x + v);
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                const float dy = qy - static_cast<float>(yb + r);
+                const float dy2 = dy * dy, dx2 = dx[0] * dx[0];
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) {
+                    const float dl = q.x - pl[r][v], da = q.y - pa[r][v], db = q.z - pb[r][v];
+                    const float s = __builtin_fmaf(db, db, __builtin_fmaf(da, da, dl * dl));
+                    const float t = VEC > 1 ? __builtin_fmaf(dx[v], dx[v], dy2)
+                                            : __builtin_fmaf(dy, dy, dx2);
+                    const float d = __builtin_fmaf(wgt, __builtin_amdgcn_sqrtf(t),
+                                                   __builtin_amdgcn_sqrtf(s));
+                    key[cc][r][v] = (__float_as_uint(d) & ~15u) | static_cast<unsigned>(4 * cr + cc);
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) {
+                lo[cr][r][v] = umin3(key[0][r][v], key[1][r][v], key[2][r][v]);
+                mid[cr][r][v] = umed3(key[0][r][v], key[1][r][v], key[2][r][v]);
+            }
+    }
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) {
+            const unsigned best = umin3(lo[0][r][v], lo[1][r][v], lo[2][r][v]);
+            const unsigned second = min(umed3(lo[0][r][v], lo[1][r][v], lo[2][r][v]),
+                                        umin3(mid[0][r][v], mid[1][r][v], mid[2][r][v]));
+            near[r][v] = second - best < kCertify;
+            cellv[r][v] = base + static_cast<int>((best >> 2) & 3u) * ncx + static_cast<int>(best & 3u);
+        }
+}
+
 // The window cell of the centre nearest to each pixel of the thread (rows yb
 // .. yb + ROWS - 1, columns x .. x + VEC - 1).  cen4, ceny, kidx: the staged
 // window of ncx columns; gx_rel: window column of the left candidates.
@@ -187,14 +236,14 @@ __device__ __forceinline__ void find_cells(const float4* cen4, const float* ceny
                                            const float (&pb)[ROWS][VEC],
                                            int (&cellv)[ROWS][VEC]) {
     int rowbase[ROWS];
-    unsigned need = 0;  // pixels whose fast argmin is not certified: bit r * VEC + v
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r) {
-        const int y = yb + r;
-        const float yf = static_cast<float>(y);
-        const int base = (g.by_S.quotient(min(y, g.h - 1)) - gy_lo - 1) * ncx + gx_rel;
-        rowbase[r] = base;
-        if constexpr (DIST == 1) {
+    for (int r = 0; r < ROWS; ++r)
+        rowbase[r] = (g.by_S.quotient(min(yb + r, g.h - 1)) - gy_lo - 1) * ncx + gx_rel;
+    if constexpr (DIST == 1) {
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            const float yf = static_cast<float>(yb + r);
+            const int base = rowbase[r];
             // exact: (distance bits, slot) as one 64-bit key, lowest slot on ties
             unsigned long long bk[VEC];
 #pragma unroll
@@ -223,57 +272,32 @@ __device__ __forceinline__ void find_cells(const float4* cen4, const float* ceny
                 const int cell = base + (slot / 3) * ncx + (slot % 3);
                 cellv[r][v] = kidx[cell] < 0 ? base + ncx + 1 : cell;
             }
-            continue;
         }
-        // the keys of one row of candidates at a time: smallest and middle of
-        // three (one instruction each), then of the three rows
-        unsigned lo[3][VEC], mid[3][VEC];
-#pragma unroll
-        for (int cr = 0; cr < 3; ++cr) {
-            unsigned key[3][VEC];
-#pragma unroll
-            for (int cc = 0; cc < 3; ++cc) {
-                const int li = base + cr * ncx + cc;
-                const float4 q = cen4[li];
-                const float dy = ceny[li] - yf;
-                const float dy2 = dy * dy;
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    const float d = eq1_fast(q.x, q.y, q.z, q.w, dy2, pl[r][v], pa[r][v], pb[r][v],
-                                             static_cast<float>(x + v), g.wgt);
-                    key[cc][v] = (__float_as_uint(d) & ~15u) | static_cast<unsigned>(4 * cr + cc);
-                }
-            }
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                lo[cr][v] = umin3(key[0][v], key[1][v], key[2][v]);
-                mid[cr][v] = umed3(key[0][v], key[1][v], key[2][v]);
-            }
-        }
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) {
-            const unsigned best = umin3(lo[0][v], lo[1][v], lo[2][v]);
-            const unsigned second = min(umed3(lo[0][v], lo[1][v], lo[2][v]),
-                                        umin3(mid[0][v], mid[1][v], mid[2][v]));
-            if (second - best < kCertify) need |= 1u << (r * VEC + v);
-            cellv[r][v] = base + static_cast<int>((best >> 2) & 3u) * ncx + static_cast<int>(best & 3u);
-        }
+        return;
     }
+    bool near[ROWS][VEC];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+        find_eq1<VEC, 1>(cen4, ceny, ncx, rowbase[r], g.wgt, x, yb + r, pl + r, pa + r, pb + r,
+                         near + r, cellv + r);
     // near ties (a few pixels per frame): the reference argmin, after the
     // fast pass, whose keys are then dead, and inline (a call would pin the
     // fast pass's live values to the callee-saved registers)
-    if (need) {
+    bool any = false;
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) any = any || near[r][v];
+    if (any) {
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
-            const int y = yb + r;
-            const int base = rowbase[r];
 #pragma unroll
             for (int v = 0; v < VEC; ++v) {
-                if (!(need & (1u << (r * VEC + v)))) continue;
-                const int slot = reference_slot(cen4, ceny, base, ncx, pl[r][v], pa[r][v],
+                if (!near[r][v]) continue;
+                const int slot = reference_slot(cen4, ceny, rowbase[r], ncx, pl[r][v], pa[r][v],
                                                 pb[r][v], static_cast<float>(x + v),
-                                                static_cast<float>(y), g.wgt);
-                cellv[r][v] = base + (slot / 3) * ncx + (slot % 3);
+                                                static_cast<float>(yb + r), g.wgt);
+                cellv[r][v] = rowbase[r] + (slot / 3) * ncx + (slot % 3);
             }
         }
     }

@@ -524,10 +524,24 @@ bool rounds_args(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int v
 
 }  // namespace
 
-bool rounds_supported(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int variant, int n) {
+// A variant that the caller chose keeps its tiles.  The built-in choice is one
+// for launches of single rounds; here small tiles pay longer, as nothing is
+// loaded or launched per round and a frame's slowest compute unit sets its
+// pace.  Per round, in us: 320 x 240 3.06 with 32 x 8 tiles, 3.15 with 32 x 16,
+// 3.93 with 64 x 16; 640 x 480 4.24 with 32 x 16, 5.05 with 64 x 16 (300 tiles
+// on 256 units); 800 x 600 4.63 and 4.95; 1024 x 1024 7.6 with 64 x 32, 8.9
+// with 64 x 16.
+int rounds_variant(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int variant, int n) {
+    if (n < kMinRounds || n > kMaxRounds) return 0;
     RoundsArgs a;
     int sources = 0;
-    return n >= kMinRounds && n <= kMaxRounds && rounds_args(ws, w, h, g, variant, compute_units(), &a, &sources);
+    const long long px = static_cast<long long>(w) * h;
+    const int cus = compute_units();
+    if (variant == assign_default_variant(w, h, g.S)) {
+        if (px <= (1ll << 17) && rounds_args(ws, w, h, g, 1, cus, &a, &sources)) return 1;
+        if (px <= (1ll << 19) && rounds_args(ws, w, h, g, 2, cus, &a, &sources)) return 2;
+    }
+    return rounds_args(ws, w, h, g, variant, cus, &a, &sources) ? variant : 0;
 }
 
 uint32_t* rounds_clear(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int variant,

@@ -156,13 +156,15 @@ hipError_t launch_assign_final_ccl(const Workspace& ws, int32_t w, int32_t h, co
                                   int64_t t, hipStream_t s);
 // Associations t0 .. t0 + n - 1 in one launch (rounds.hip), with the labels
 // of the last one (store_last) and its sums in the ring (sums_last: another
-// association follows).  Only where rounds_supported.  The words that
+// association follows).  `variant` names the tiles: rounds_variant gives those
+// for n rounds of a context with an association variant, 0 where the frame
+// does not suit.  The words that
 // rounds_clear names must be zero: `cleared` says that an earlier launch of
 // the stream has done so, else the call does.
 // census_ticks: how long a workgroup waits for the others to start, in
 // 10 ns (negative: the built-in time).
 constexpr int kMinRounds = 2;
-bool rounds_supported(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int variant, int n);
+int rounds_variant(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int variant, int n);
 uint32_t* rounds_clear(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int variant,
                        size_t* words);
 hipError_t launch_rounds(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int64_t t0, int n,
