@@ -8,8 +8,9 @@
 // (v_mfma_f32_16x16x32_bf16).
 //
 // Layouts.  Activations are NHWC over a batch of equally sized crops,
-// element ((n H + y) W + x) C + c, with C = 32 bf16 channels for the input
-// (3 used: L/100, a/128, b/128), both hidden layers and the gradients, and
+// element ((n H + y) W + x) C + c, with C = 32 bf16 channels for both hidden
+// layers and the gradients, C = 4 for the input (L/100, a/128, b/128, 0: the
+// other 28 inputs of a matrix operand are zeros made in registers), and
 // C = 16 FP32 for the logits (9 used).  Zero padding at every crop border.
 // Parameters are one FP32 vector: W1[9][32][3], b1[32], W2[9][32][32], b2[32],
 // W3[9][9][32], b3[9], P[S*S][9], with tap = (dy + 1) * 3 + (dx + 1) reading
@@ -46,6 +47,7 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kC = 32;   // hidden (and padded input) channels
 constexpr int kC3 = 9;   // classes
+constexpr int kXC = 4;   // stored input channels (L/100, a/128, b/128, 0)
 constexpr int kOffW1 = 0, kOffB1 = 9 * kC * 3, kOffW2 = kOffB1 + kC;
 constexpr int kOffB2 = kOffW2 + 9 * kC * kC, kOffW3 = kOffB2 + kC;
 constexpr int kOffB3 = kOffW3 + 9 * kC3 * kC, kOffP = kOffB3 + kC3;
@@ -120,18 +122,12 @@ __global__ __launch_bounds__(256) void input_kernel(CropTable ct, int cw, int ch
     if (px >= per) return;
     const NetCrop& c = ct.c[n];
     const int gx = c.ox + px % cw, gy = c.oy + px / cw;
-    u32x4 v0 = {0u, 0u, 0u, 0u};
+    uint2 v = make_uint2(0u, 0u);
     if (gx < c.img_w && gy < c.img_h) {
         const size_t gi = static_cast<size_t>(gy) * c.img_w + gx;
-        v0.x = pack2(c.L[gi] / 100.0f, c.A[gi] / 128.0f);
-        v0.y = pack2(c.B[gi] / 128.0f, 0.0f);
+        v = make_uint2(pack2(c.L[gi] / 100.0f, c.A[gi] / 128.0f), pack2(c.B[gi] / 128.0f, 0.0f));
     }
-    u32x4* out = reinterpret_cast<u32x4*>(x + (static_cast<size_t>(n) * per + px) * kC);
-    const u32x4 z = {0u, 0u, 0u, 0u};
-    out[0] = v0;
-    out[1] = z;
-    out[2] = z;
-    out[3] = z;
+    *reinterpret_cast<uint2*>(x + (static_cast<size_t>(n) * per + px) * kXC) = v;
 }
 
 // ------------------------------------------------- MFMA 3x3 convolution
@@ -144,23 +140,36 @@ enum ConvMode { kFwdRelu = 0, kFwdLogits = 1, kBwdMasked = 2 };
 constexpr int kTW = 64, kTRows = 4;
 constexpr int kSW = kTW + 2, kSRows = kTRows + 2, kPS = 40;
 
-template <int MT, int MODE>
+// IC: stored input channels, 32, or 4 (the net's input: lanes of the other
+// channels supply zeros).
+template <int MT, int MODE, int IC = kC>
 __global__ __launch_bounds__(256) void conv_kernel(
     const unsigned short* __restrict__ in, const unsigned short* __restrict__ Wb,
     const float* __restrict__ bias, const float* __restrict__ P, CropTable ct, int S, int cw,
     int ch, const unsigned short* __restrict__ mask, unsigned short* __restrict__ out16,
     float* __restrict__ out32) {
-    __shared__ __align__(16) unsigned short tile[kSRows * kSW * kPS];
+    constexpr int kStride = IC == kC ? kPS : IC;  // elements per staged pixel
+    __shared__ __align__(16) unsigned short tile[kSRows * kSW * kStride];
     const int n = blockIdx.z;
     const int x0 = blockIdx.x * kTW, y0 = blockIdx.y * kTRows;
     const size_t base = static_cast<size_t>(n) * cw * ch;
-    for (int i = threadIdx.x; i < kSRows * kSW * 4; i += 256) {
-        const int q = i / 4, part = i % 4;
-        const int sx = x0 - 1 + q % kSW, sy = y0 - 1 + q / kSW;
-        u32x4 v = {0u, 0u, 0u, 0u};
-        if (sx >= 0 && sy >= 0 && sx < cw && sy < ch)
-            v = reinterpret_cast<const u32x4*>(in + (base + static_cast<size_t>(sy) * cw + sx) * kC)[part];
-        *reinterpret_cast<u32x4*>(tile + q * kPS + part * 8) = v;
+    if constexpr (IC == kC) {
+        for (int i = threadIdx.x; i < kSRows * kSW * 4; i += 256) {
+            const int q = i / 4, part = i % 4;
+            const int sx = x0 - 1 + q % kSW, sy = y0 - 1 + q / kSW;
+            u32x4 v = {0u, 0u, 0u, 0u};
+            if (sx >= 0 && sy >= 0 && sx < cw && sy < ch)
+                v = reinterpret_cast<const u32x4*>(in + (base + static_cast<size_t>(sy) * cw + sx) * kC)[part];
+            *reinterpret_cast<u32x4*>(tile + q * kPS + part * 8) = v;
+        }
+    } else {
+        for (int q = threadIdx.x; q < kSRows * kSW; q += 256) {
+            const int sx = x0 - 1 + q % kSW, sy = y0 - 1 + q / kSW;
+            uint2 v = make_uint2(0u, 0u);
+            if (sx >= 0 && sy >= 0 && sx < cw && sy < ch)
+                v = *reinterpret_cast<const uint2*>(in + (base + static_cast<size_t>(sy) * cw + sx) * IC);
+            *reinterpret_cast<uint2*>(tile + q * kStride) = v;
+        }
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int row = lane & 15, kq = lane >> 4;
@@ -184,8 +193,15 @@ __global__ __launch_bounds__(256) void conv_kernel(
         for (int t = 0; t < 9; ++t) {
             // staged position of input pixel (xs + row + dx, y + dy)
             const int q = (wave + t / 3) * kSW + nt * 16 + row + t % 3;
-            const bf16x8 b =
-                __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(tile + q * kPS + kq * 8));
+            u32x4 bits = {0u, 0u, 0u, 0u};
+            if constexpr (IC == kC) {
+                bits = *reinterpret_cast<const u32x4*>(tile + q * kPS + kq * 8);
+            } else {
+                const uint2 v = *reinterpret_cast<const uint2*>(tile + q * kStride);
+                bits.x = kq == 0 ? v.x : 0u;
+                bits.y = kq == 0 ? v.y : 0u;
+            }
+            const bf16x8 b = __builtin_bit_cast(bf16x8, bits);
 #pragma unroll
             for (int m = 0; m < MT; ++m)
                 acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[t][m], b, acc[m], 0, 0, 0);
@@ -212,13 +228,21 @@ __global__ __launch_bounds__(256) void conv_kernel(
                 const NetCrop& c = ct.c[n];
                 const bool inside = c.ox + x < c.img_w && c.oy + y < c.img_h;
                 float r[4];
+                unsigned short mk[4] = {};
+                if constexpr (MODE == kBwdMasked) {
+                    const uint2 mv = *reinterpret_cast<const uint2*>(mask + pi * kC + o0);
+                    mk[0] = static_cast<unsigned short>(mv.x);
+                    mk[1] = static_cast<unsigned short>(mv.x >> 16);
+                    mk[2] = static_cast<unsigned short>(mv.y);
+                    mk[3] = static_cast<unsigned short>(mv.y >> 16);
+                }
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     float v = acc[m][i];
                     if constexpr (MODE == kFwdRelu) {
                         v = inside ? fmaxf(v + bias[o0 + i], 0.0f) : 0.0f;
                     } else {  // through the ReLU that produced this layer's input
-                        if (!(bf16_float(mask[pi * kC + o0 + i]) > 0.0f)) v = 0.0f;
+                        if (!(bf16_float(mk[i]) > 0.0f)) v = 0.0f;
                     }
                     r[i] = v;
                 }
@@ -334,86 +358,130 @@ __global__ __launch_bounds__(256) void loss_kernel(const float* __restrict__ log
 // dW[t][o][i] = sum over pixels p of dz[p][o] * a[p + d_t][i] (and, with a
 // bias, db[o] = sum dz[p][o]) over a strip of kGW x kGStrip pixels of one
 // crop, kGR rows at a time.  dz and the input (with halo) are staged in LDS
-// channel-blocked: element (r, x, c) at ((r * chunks + x / 8) * 32 + c) * 8 +
-// x % 8, so a lane's eight pixels of one channel are one 16-byte read; the
-// one-pixel shifts of the taps are funnel shifts of neighbouring words.
-// Wavefront w takes output tile m and input tile ni (two output tiles x two
-// input tiles for MO = 2; for MO = 1 wavefronts 2, 3 take the odd rows and
-// add into 0, 1 at the end), all nine taps.
+// channel-blocked: the eight pixels x / 8 of row r and channel c are 16 bytes
+// at (r * chunks + x / 8) * kGBlock + 16 c, so a lane's eight pixels of one
+// channel are one 16-byte read; the one-pixel shifts of the taps are funnel
+// shifts of neighbouring words.  A thread turns 8 pixels x 8 channels (eight
+// 16-byte loads) in registers into eight 16-byte LDS writes; the next rows'
+// loads are in flight during the matrix products.  The bias is one more
+// product, with ones.
+// What bounds it: the staging (element by element it was 64 two-byte LDS
+// writes with bank conflicts per thread, and the bias 256 serial LDS reads by
+// one wavefront: 52 us per 32 x 32 layer of 32 crops of 128 x 128).
+// Eight wavefronts take (output tile, input tile, row group): two output
+// tiles x two input tiles x two groups of rows, or one of either and four;
+// the groups' sums are added in LDS in a fixed order.
 constexpr int kGW = 64, kGR = 4, kGStrip = 32;
 constexpr int kGZChunks = kGW / 8;       // dz: columns x0 .. x0 + 63
 constexpr int kGAChunks = kGW / 8 + 2;   // input: columns x0 - 8 .. x0 + 71
+constexpr int kGThreads = 512;
+constexpr int kGBlock = kC * 16 + 16;    // bytes per 8 pixels (padded: banks)
 
-template <int MO>
-__global__ __launch_bounds__(256) void wgrad_kernel(const unsigned short* __restrict__ dz,
-                                                    const unsigned short* __restrict__ a, int cw,
-                                                    int ch, int cout, int cin_keep, int has_bias,
-                                                    float* __restrict__ partial, int region) {
-    __shared__ __align__(16) unsigned short sdz[kGR * kGZChunks * kC * 8];
-    __shared__ __align__(16) unsigned short sa[(kGR + 2) * kGAChunks * kC * 8];
+// 8 pixels x 8 channels (v[p]: channels 2 j, 2 j + 1 of pixel p in word j) to
+// the eight pixels of each channel.
+__device__ __forceinline__ void transpose8(const u32x4 (&v)[8], unsigned char* lds) {
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        u32x4 o;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const unsigned lo = v[2 * k][c / 2], hi = v[2 * k + 1][c / 2];
+            o[k] = (c & 1) ? __builtin_amdgcn_perm(hi, lo, 0x07060302u)
+                           : __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+        }
+        *reinterpret_cast<u32x4*>(lds + c * 16) = o;
+    }
+}
+
+// MO: output tiles (16 channels each); AC: stored input channels, 32 or 4.
+template <int MO, int AC>
+__global__ __launch_bounds__(kGThreads) void wgrad_kernel(const unsigned short* __restrict__ dz,
+                                                          const unsigned short* __restrict__ a,
+                                                          int cw, int ch, int cout, int cin_keep,
+                                                          int has_bias,
+                                                          float* __restrict__ partial, int region) {
+    constexpr int kNI = AC == kC ? 2 : 1;             // input tiles
+    constexpr int kRoles = MO * kNI;                  // wavefronts per row group
+    constexpr int kGroups = kGThreads / 64 / kRoles;  // row groups
+    constexpr int kZTasks = kGR * kGZChunks * 4, kAParts = AC == kC ? 4 : 1;
+    constexpr int kATasks = (kGR + 2) * kGAChunks * kAParts;
+    static_assert(kZTasks + kATasks <= kGThreads, "one staging task per thread");
+    __shared__ __align__(16) unsigned char lds[(kGR * kGZChunks + (kGR + 2) * kGAChunks) * kGBlock];
+    unsigned char* const sdz = lds;
+    unsigned char* const sa = lds + kGR * kGZChunks * kGBlock;
+    static_assert(kRoles * 10 * 4 * 64 * sizeof(float) <= sizeof(lds), "the groups' sums fit");
     const int n = blockIdx.z;
     const int x0 = blockIdx.x * kGW;
     const size_t base = static_cast<size_t>(n) * cw * ch;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int row = lane & 15, kq = lane >> 4;
-    const int m = MO == 2 ? wave >> 1 : 0;
-    const int ni = wave & 1;
-    f32x4 acc[9];
-#pragma unroll
-    for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    float bsum = 0.0f;
+    const int role = wave % kRoles, group = wave / kRoles;
+    const int m = role % MO, ni = role / MO;
 
+    // this thread's staging task: 8 pixels of row tr (dz rows from y0, input
+    // rows from y0 - 1), columns tx .. tx + 7, channels 8 part ..
+    const bool is_z = threadIdx.x < kZTasks;
+    const int task = is_z ? threadIdx.x : threadIdx.x - kZTasks;
+    const bool busy = is_z || task < kATasks;
+    const int parts = is_z ? 4 : kAParts, chunks = is_z ? kGZChunks : kGAChunks;
+    const int part = task % parts, tc = task / parts % chunks, tr = task / parts / chunks;
+    const int tx = x0 + tc * 8 - (is_z ? 0 : 8);
+    unsigned char* const dst = (is_z ? sdz : sa) + (tr * chunks + tc) * kGBlock + part * 8 * 16;
+    u32x4 v[8];
+    auto fetch = [&](int chunk) {
+        const int y = blockIdx.y * kGStrip + chunk * kGR + tr - (is_z ? 0 : 1);
+        const bool row_ok = busy && y >= 0 && y < ch;
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {
+            const int x = tx + p;
+            v[p] = u32x4{0u, 0u, 0u, 0u};
+            if (row_ok && x >= 0 && x < cw) {
+                const size_t pi = base + static_cast<size_t>(y) * cw + x;
+                if (is_z || AC == kC) {
+                    v[p] = reinterpret_cast<const u32x4*>((is_z ? dz : a) + pi * kC)[part];
+                } else {
+                    const uint2 q = *reinterpret_cast<const uint2*>(a + pi * AC);
+                    v[p].x = q.x;
+                    v[p].y = q.y;
+                }
+            }
+        }
+    };
+
+    f32x4 acc[10];  // the nine taps, the bias
+#pragma unroll
+    for (int t = 0; t < 10; ++t) acc[t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const unsigned one2 = 0x3F803F80u;  // two ones in bf16
+    const bf16x8 ones = __builtin_bit_cast(bf16x8, u32x4{one2, one2, one2, one2});
+
+    fetch(0);
     for (int chunk = 0; chunk < kGStrip / kGR; ++chunk) {
         const int y0 = blockIdx.y * kGStrip + chunk * kGR;
         if (y0 >= ch) break;
-        for (int i = threadIdx.x; i < kGR * kGW * 4; i += 256) {
-            const int q = i >> 2, part = i & 3;
-            const int r = q / kGW, xx = q % kGW;
-            const int x = x0 + xx, y = y0 + r;
-            u32x4 v = {0u, 0u, 0u, 0u};
-            if (x < cw && y < ch)
-                v = reinterpret_cast<const u32x4*>(dz + (base + static_cast<size_t>(y) * cw + x) * kC)[part];
-            unsigned short* d = sdz + ((r * kGZChunks + xx / 8) * kC + part * 8) * 8 + xx % 8;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                d[(2 * j) * 8] = static_cast<unsigned short>(v[j] & 0xFFFFu);
-                d[(2 * j + 1) * 8] = static_cast<unsigned short>(v[j] >> 16);
-            }
-        }
-        for (int i = threadIdx.x; i < (kGR + 2) * kGAChunks * 8 * 4; i += 256) {
-            const int q = i >> 2, part = i & 3;
-            const int r = q / (kGAChunks * 8), xs = q % (kGAChunks * 8);
-            const int x = x0 - 8 + xs, y = y0 - 1 + r;
-            u32x4 v = {0u, 0u, 0u, 0u};
-            if (x >= 0 && y >= 0 && x < cw && y < ch)
-                v = reinterpret_cast<const u32x4*>(a + (base + static_cast<size_t>(y) * cw + x) * kC)[part];
-            unsigned short* d = sa + ((r * kGAChunks + xs / 8) * kC + part * 8) * 8 + xs % 8;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                d[(2 * j) * 8] = static_cast<unsigned short>(v[j] & 0xFFFFu);
-                d[(2 * j + 1) * 8] = static_cast<unsigned short>(v[j] >> 16);
-            }
-        }
+        if (busy) transpose8(v, dst);
         __syncthreads();
-        if (has_bias && static_cast<int>(threadIdx.x) < cout) {
-            for (int r = 0; r < kGR; ++r)
-                for (int c8 = 0; c8 < kGZChunks; ++c8)
-                    for (int e = 0; e < 8; ++e)
-                        bsum += bf16_float(sdz[((r * kGZChunks + c8) * kC + threadIdx.x) * 8 + e]);
-        }
-        for (int r = (MO == 2 ? 0 : wave >> 1); r < kGR; r += (MO == 2 ? 1 : 2)) {
+        if (chunk + 1 < kGStrip / kGR && y0 + kGR < ch) fetch(chunk + 1);
+#pragma unroll
+        for (int rr = 0; rr < kGR / kGroups; ++rr) {
+            const int r = group + rr * kGroups;
 #pragma unroll
             for (int kk = 0; kk < kGW / 32; ++kk) {
                 const int c8 = kk * 4 + kq;  // chunk of this lane's 8 pixels
                 const bf16x8 av = __builtin_bit_cast(
-                    bf16x8, *reinterpret_cast<const u32x4*>(
-                                sdz + ((r * kGZChunks + c8) * kC + m * 16 + row) * 8));
+                    bf16x8, *reinterpret_cast<const u32x4*>(sdz + (r * kGZChunks + c8) * kGBlock +
+                                                            (m * 16 + row) * 16));
+                if (has_bias && ni == 0)
+                    acc[9] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, ones, acc[9], 0, 0, 0);
 #pragma unroll
                 for (int dy = 0; dy < 3; ++dy) {
-                    const unsigned short* srow = sa + (((r + dy) * kGAChunks) * kC + ni * 16 + row) * 8;
-                    const u32x4 w1 = *reinterpret_cast<const u32x4*>(srow + (c8 + 1) * kC * 8);
-                    const unsigned w0 = *reinterpret_cast<const unsigned*>(srow + c8 * kC * 8 + 6);
-                    const unsigned w2 = *reinterpret_cast<const unsigned*>(srow + (c8 + 2) * kC * 8);
+                    const unsigned char* srow = sa + (r + dy) * kGAChunks * kGBlock + (ni * 16 + row) * 16;
+                    u32x4 w1 = *reinterpret_cast<const u32x4*>(srow + (c8 + 1) * kGBlock);
+                    unsigned w0 = *reinterpret_cast<const unsigned*>(srow + c8 * kGBlock + 12);
+                    unsigned w2 = *reinterpret_cast<const unsigned*>(srow + (c8 + 2) * kGBlock);
+                    if (AC != kC && row >= AC) {  // no such channel
+                        w1 = u32x4{0u, 0u, 0u, 0u};
+                        w0 = w2 = 0u;
+                    }
                     const u32x4 bl = {mid16(w1.x, w0), mid16(w1.y, w1.x), mid16(w1.z, w1.y),
                                       mid16(w1.w, w1.z)};
                     const u32x4 br = {mid16(w1.y, w1.x), mid16(w1.z, w1.y), mid16(w1.w, w1.z),
@@ -430,33 +498,39 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const unsigned short* __rest
         __syncthreads();
     }
 
+    // the row groups' sums, the last into the one before, and so on
+    float* const red = reinterpret_cast<float*>(lds) + role * 10 * 4 * 64 + lane;
+    for (int gi = kGroups - 1; gi > 0; --gi) {
+        if (group == gi)
+#pragma unroll
+            for (int t = 0; t < 10; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) red[(t * 4 + i) * 64] = acc[t][i];
+        __syncthreads();
+        if (group == gi - 1)
+#pragma unroll
+            for (int t = 0; t < 10; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[t][i] += red[(t * 4 + i) * 64];
+        __syncthreads();
+    }
+    if (group != 0) return;
     float* out = partial + static_cast<size_t>(blockIdx.z * gridDim.y * gridDim.x +
                                                blockIdx.y * gridDim.x + blockIdx.x) * region;
-    if (MO == 1) {  // fold the odd-row wavefronts into the even-row ones
-        float* red = reinterpret_cast<float*>(sa);
-        if (wave >= 2)
+    const int in = ni * 16 + row;
 #pragma unroll
-            for (int t = 0; t < 9; ++t)
+    for (int t = 0; t < 9; ++t)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) red[((wave - 2) * 36 + t * 4 + i) * 64 + lane] = acc[t][i];
-        __syncthreads();
-        if (wave < 2)
+        for (int i = 0; i < 4; ++i) {
+            const int o = m * 16 + kq * 4 + i;
+            if (o < cout && in < cin_keep) out[(t * cout + o) * cin_keep + in] = acc[t][i];
+        }
+    if (has_bias && ni == 0 && row == 0)
 #pragma unroll
-            for (int t = 0; t < 9; ++t)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[t][i] += red[(wave * 36 + t * 4 + i) * 64 + lane];
-    }
-    if (MO == 2 || wave < 2) {
-        const int in = ni * 16 + row;
-#pragma unroll
-        for (int t = 0; t < 9; ++t)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int o = m * 16 + kq * 4 + i;
-                if (o < cout && in < cin_keep) out[(t * cout + o) * cin_keep + in] = acc[t][i];
-            }
-    }
-    if (has_bias && static_cast<int>(threadIdx.x) < cout) out[9 * cout * cin_keep + threadIdx.x] = bsum;
+        for (int i = 0; i < 4; ++i) {
+            const int o = m * 16 + kq * 4 + i;
+            if (o < cout) out[9 * cout * cin_keep + o] = acc[9][i];
+        }
 }
 
 // Sum of the partial gradients in block order, scaled by 1 / count.
@@ -465,28 +539,64 @@ struct GradRegions {
     int start[4], size[4], nblk[4];
 };
 
-__global__ void reduce_kernel(GradRegions r, int count, const double* __restrict__ lossp,
-                              int nloss, float* __restrict__ grad, double* __restrict__ loss) {
-    __shared__ double s_inv;
-    if (threadIdx.x == 0) {
-        double tl = 0.0, tn = 0.0;
-        for (int b = 0; b < nloss; ++b) {
-            tl += lossp[2 * b];
-            tn += lossp[2 * b + 1];
+// A workgroup takes kRedParams parameters, kRedSlices threads each: a slice
+// sums every kRedSlices-th partial, and the slices' sums are added in order.
+// (One thread per parameter, 256 dependent additions behind as many loads,
+// and a serial sum of the loss terms in every workgroup took 77 us.)
+constexpr int kRedParams = 64, kRedSlices = 16;
+
+__global__ __launch_bounds__(kRedParams* kRedSlices) void reduce_kernel(
+    GradRegions r, int count, const double* __restrict__ lossp, int nloss,
+    float* __restrict__ grad, double* __restrict__ loss) {
+    __shared__ double sums[kRedSlices][kRedParams];
+    __shared__ double s_l[kRedSlices], s_n[kRedSlices];
+    const int p = threadIdx.x % kRedParams, slice = threadIdx.x / kRedParams;
+    const int i = blockIdx.x * kRedParams + p;
+    double s = 0.0;
+    if (i < count) {
+        int j = 0;
+        while (j < 3 && i >= r.start[j] + r.size[j]) ++j;
+        const int sz = r.size[j], nblk = r.nblk[j];
+        const float* q = r.part[j] + (i - r.start[j]);
+        int b = slice;
+        for (; b + 7 * kRedSlices < nblk; b += 8 * kRedSlices) {  // eight loads in flight
+            float f[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) f[u] = q[static_cast<size_t>(b + u * kRedSlices) * sz];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += static_cast<double>(f[u]);
         }
-        s_inv = tn > 0.0 ? 1.0 / tn : 0.0;
-        if (blockIdx.x == 0 && loss) *loss = tl * s_inv;
+        for (; b < nblk; b += kRedSlices) s += static_cast<double>(q[static_cast<size_t>(b) * sz]);
+    }
+    sums[slice][p] = s;
+    // the loss terms and the counts (whole numbers): a thread's own, then its
+    // wavefront's (one slice), then the slices in order
+    double tl = 0.0, tn = 0.0;
+    for (int b = threadIdx.x; b < nloss; b += kRedParams * kRedSlices) {
+        tl += lossp[2 * b];
+        tn += lossp[2 * b + 1];
+    }
+    for (int d = 32; d > 0; d >>= 1) {
+        tl += __shfl_xor(tl, d);
+        tn += __shfl_xor(tn, d);
+    }
+    if (p == 0) {
+        s_l[slice] = tl;
+        s_n[slice] = tn;
     }
     __syncthreads();
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (slice != 0) return;
+    tl = tn = 0.0;
+    for (int k = 0; k < kRedSlices; ++k) {
+        tl += s_l[k];
+        tn += s_n[k];
+    }
+    const double inv = tn > 0.0 ? 1.0 / tn : 0.0;
+    if (blockIdx.x == 0 && p == 0 && loss) *loss = tl * inv;
     if (i >= count) return;
-    int j = 0;
-    while (j < 3 && i >= r.start[j] + r.size[j]) ++j;
-    const int li = i - r.start[j], sz = r.size[j];
-    const float* p = r.part[j];
-    double s = 0.0;
-    for (int b = 0; b < r.nblk[j]; ++b) s += static_cast<double>(p[static_cast<size_t>(b) * sz + li]);
-    grad[i] = static_cast<float>(s * s_inv);
+    s = sums[0][p];
+    for (int k = 1; k < kRedSlices; ++k) s += sums[k][p];
+    grad[i] = static_cast<float>(s * inv);
 }
 
 __global__ void adam_kernel(float* __restrict__ p, const float* __restrict__ g,
@@ -1042,7 +1152,7 @@ size_t net_layout(int n, int cw, int ch, int S, int mode, NetWs* nw, char* base)
     w.wt.W2t = reinterpret_cast<unsigned short*>(take(9 * kC * kC * 2));
     w.wt.W3t = reinterpret_cast<unsigned short*>(take(9 * kC * kC * 2));
     if (mode >= kForward) {
-        w.x = reinterpret_cast<unsigned short*>(take(P * kC * 2));
+        w.x = reinterpret_cast<unsigned short*>(take(P * kXC * 2));
         w.a1 = reinterpret_cast<unsigned short*>(take(P * kC * 2));
         w.a2 = reinterpret_cast<unsigned short*>(take(P * kC * 2));
         w.logits = reinterpret_cast<float*>(take(P * 16 * sizeof(float)));
@@ -1116,8 +1226,9 @@ hipError_t enqueue_forward(const NetWs& nw, const CropTable& ct, int n, int cw, 
     const dim3 grid((cw + kTW - 1) / kTW, (ch + kTRows - 1) / kTRows, n);
     {
         KernelTimer t("net_conv1", s);
-        conv_kernel<2, kFwdRelu><<<grid, 256, 0, s>>>(nw.x, nw.wt.W1b, params + kOffB1, nullptr, ct,
-                                                      S, cw, ch, nullptr, nw.a1, nullptr);
+        conv_kernel<2, kFwdRelu, kXC><<<grid, 256, 0, s>>>(nw.x, nw.wt.W1b, params + kOffB1,
+                                                           nullptr, ct, S, cw, ch, nullptr, nw.a1,
+                                                           nullptr);
     }
     {
         KernelTimer t("net_conv2", s);
@@ -1145,7 +1256,7 @@ hipError_t enqueue_backward(const NetWs& nw, const CropTable& ct, int n, int cw,
     const dim3 cgrid((cw + kTW - 1) / kTW, (ch + kTRows - 1) / kTRows, n);
     {
         KernelTimer t("net_wgrad3", s);
-        wgrad_kernel<1><<<ggrid, 256, 0, s>>>(nw.dz3, nw.a2, cw, ch, kC3, kC, 0, nw.part_w3,
+        wgrad_kernel<1, kC><<<ggrid, kGThreads, 0, s>>>(nw.dz3, nw.a2, cw, ch, kC3, kC, 0, nw.part_w3,
                                               kOffB3 - kOffW3);
     }
     {
@@ -1155,7 +1266,7 @@ hipError_t enqueue_backward(const NetWs& nw, const CropTable& ct, int n, int cw,
     }
     {
         KernelTimer t("net_wgrad2", s);
-        wgrad_kernel<2><<<ggrid, 256, 0, s>>>(nw.dz2, nw.a1, cw, ch, kC, kC, 1, nw.part_w2,
+        wgrad_kernel<2, kC><<<ggrid, kGThreads, 0, s>>>(nw.dz2, nw.a1, cw, ch, kC, kC, 1, nw.part_w2,
                                               kOffW3 - kOffW2);
     }
     unsigned short* dz1 = nw.dz3;
@@ -1166,7 +1277,7 @@ hipError_t enqueue_backward(const NetWs& nw, const CropTable& ct, int n, int cw,
     }
     {
         KernelTimer t("net_wgrad1", s);
-        wgrad_kernel<2><<<ggrid, 256, 0, s>>>(dz1, nw.x, cw, ch, kC, 3, 1, nw.part_w1,
+        wgrad_kernel<2, kXC><<<ggrid, kGThreads, 0, s>>>(dz1, nw.x, cw, ch, kC, 3, 1, nw.part_w1,
                                               kOffW2 - kOffW1);
     }
     GradRegions r;
@@ -1189,7 +1300,8 @@ hipError_t enqueue_backward(const NetWs& nw, const CropTable& ct, int n, int cw,
     const int count = kOffP + kC3 * S * S;
     {
         KernelTimer t("net_reduce", s);
-        reduce_kernel<<<(count + 255) / 256, 256, 0, s>>>(r, count, nw.lossp, nw.nb_loss, grad, loss);
+        reduce_kernel<<<(count + kRedParams - 1) / kRedParams, kRedParams * kRedSlices, 0, s>>>(
+            r, count, nw.lossp, nw.nb_loss, grad, loss);
     }
     return hipGetLastError();
 }
