@@ -138,6 +138,7 @@ __global__ __launch_bounds__(256) void input_kernel(CropTable ct, int cw, int ch
 enum ConvMode { kFwdRelu = 0, kFwdLogits = 1, kBwdMasked = 2 };
 
 constexpr int kTW = 64, kTRows = 4;
+constexpr int kTSteps = 2;  // tiles per workgroup (the weights are loaded once for both)
 constexpr int kSW = kTW + 2, kSRows = kTRows + 2, kPS = 40;
 
 // IC: stored input channels, 32, or 4 (the net's input: lanes of the other
@@ -151,26 +152,8 @@ __global__ __launch_bounds__(256) void conv_kernel(
     constexpr int kStride = IC == kC ? kPS : IC;  // elements per staged pixel
     __shared__ __align__(16) unsigned short tile[kSRows * kSW * kStride];
     const int n = blockIdx.z;
-    const int x0 = blockIdx.x * kTW, y0 = blockIdx.y * kTRows;
+    const int x0 = blockIdx.x * kTW;
     const size_t base = static_cast<size_t>(n) * cw * ch;
-    if constexpr (IC == kC) {
-        for (int i = threadIdx.x; i < kSRows * kSW * 4; i += 256) {
-            const int q = i / 4, part = i % 4;
-            const int sx = x0 - 1 + q % kSW, sy = y0 - 1 + q / kSW;
-            u32x4 v = {0u, 0u, 0u, 0u};
-            if (sx >= 0 && sy >= 0 && sx < cw && sy < ch)
-                v = reinterpret_cast<const u32x4*>(in + (base + static_cast<size_t>(sy) * cw + sx) * kC)[part];
-            *reinterpret_cast<u32x4*>(tile + q * kPS + part * 8) = v;
-        }
-    } else {
-        for (int q = threadIdx.x; q < kSRows * kSW; q += 256) {
-            const int sx = x0 - 1 + q % kSW, sy = y0 - 1 + q / kSW;
-            uint2 v = make_uint2(0u, 0u);
-            if (sx >= 0 && sy >= 0 && sx < cw && sy < ch)
-                v = *reinterpret_cast<const uint2*>(in + (base + static_cast<size_t>(sy) * cw + sx) * IC);
-            *reinterpret_cast<uint2*>(tile + q * kStride) = v;
-        }
-    }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int row = lane & 15, kq = lane >> 4;
     bf16x8 wa[9][MT];
@@ -180,74 +163,102 @@ __global__ __launch_bounds__(256) void conv_kernel(
         for (int m = 0; m < MT; ++m)
             wa[t][m] = __builtin_bit_cast(
                 bf16x8, *reinterpret_cast<const u32x4*>(Wb + ((t * MT * 16 + m * 16 + row) * kC + kq * 8)));
-    __syncthreads();
-    const int y = y0 + wave;
-    if (y >= ch) return;
-    for (int nt = 0; nt < kTW / 16; ++nt) {
-        const int xs = x0 + nt * 16;
-        if (xs >= cw) break;
-        f32x4 acc[MT];
+    for (int step = 0; step < kTSteps; ++step) {
+        const int y0 = (blockIdx.y * kTSteps + step) * kTRows;
+        if (y0 >= ch) break;
+        if (step > 0) __syncthreads();  // the last tile is read
+        // every load first (from a clamped position, so without a branch around
+        // it), then the LDS writes: one trip through memory per tile
+        {
+            using Part = std::conditional_t<IC == kC, u32x4, uint2>;  // 8 channels, or all 4
+            constexpr int kParts = IC == kC ? 4 : 1, kItems = kSRows * kSW * kParts;
+            constexpr int kSlots = (kItems + 255) / 256;
+            Part v[kSlots];
+            bool ok[kSlots];
 #pragma unroll
-        for (int m = 0; m < MT; ++m) acc[m] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int t = 0; t < 9; ++t) {
-            // staged position of input pixel (xs + row + dx, y + dy)
-            const int q = (wave + t / 3) * kSW + nt * 16 + row + t % 3;
-            u32x4 bits = {0u, 0u, 0u, 0u};
-            if constexpr (IC == kC) {
-                bits = *reinterpret_cast<const u32x4*>(tile + q * kPS + kq * 8);
-            } else {
-                const uint2 v = *reinterpret_cast<const uint2*>(tile + q * kStride);
-                bits.x = kq == 0 ? v.x : 0u;
-                bits.y = kq == 0 ? v.y : 0u;
+            for (int u = 0; u < kSlots; ++u) {
+                const int q = (threadIdx.x + u * 256) / kParts, part = (threadIdx.x + u * 256) % kParts;
+                const int sx = x0 - 1 + q % kSW, sy = y0 - 1 + q / kSW;
+                ok[u] = sx >= 0 && sy >= 0 && sx < cw && sy < ch;
+                const size_t pi = base + static_cast<size_t>(min(max(sy, 0), ch - 1)) * cw +
+                                  min(max(sx, 0), cw - 1);
+                v[u] = reinterpret_cast<const Part*>(in + pi * IC)[part];
             }
-            const bf16x8 b = __builtin_bit_cast(bf16x8, bits);
 #pragma unroll
-            for (int m = 0; m < MT; ++m)
-                acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[t][m], b, acc[m], 0, 0, 0);
+            for (int u = 0; u < kSlots; ++u) {
+                const int i = threadIdx.x + u * 256;
+                if (i < kItems)
+                    *reinterpret_cast<Part*>(tile + i / kParts * kStride + i % kParts * 8) = ok[u] ? v[u] : Part{};
+            }
         }
-        // lane holds output channels 16 m + 4 kq + i of pixel xs + row
-        const int x = xs + row;
-        if (x >= cw) continue;
-        const size_t pi = base + static_cast<size_t>(y) * cw + x;
+        __syncthreads();
+        const int y = y0 + wave;
+        for (int nt = 0; nt < kTW / 16 && y < ch; ++nt) {
+            const int xs = x0 + nt * 16;
+            if (xs >= cw) break;
+            f32x4 acc[MT];
 #pragma unroll
-        for (int m = 0; m < MT; ++m) {
-            const int o0 = m * 16 + kq * 4;
-            if constexpr (MODE == kFwdLogits) {
-                const NetCrop& c = ct.c[n];
-                const int ph = ((c.oy + y) % S) * S + (c.ox + x) % S;
-                f32x4 v;
+            for (int m = 0; m < MT; ++m) acc[m] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int o = o0 + i;
-                    v[i] = o < kC3 ? acc[m][i] + bias[o] + P[ph * kC3 + o] : 0.0f;
+            for (int t = 0; t < 9; ++t) {
+                // staged position of input pixel (xs + row + dx, y + dy)
+                const int q = (wave + t / 3) * kSW + nt * 16 + row + t % 3;
+                u32x4 bits = {0u, 0u, 0u, 0u};
+                if constexpr (IC == kC) {
+                    bits = *reinterpret_cast<const u32x4*>(tile + q * kPS + kq * 8);
+                } else {
+                    const uint2 v = *reinterpret_cast<const uint2*>(tile + q * kStride);
+                    bits.x = kq == 0 ? v.x : 0u;
+                    bits.y = kq == 0 ? v.y : 0u;
                 }
-                *reinterpret_cast<f32x4*>(out32 + pi * 16 + o0) = v;
-            } else {
-                // a hidden activation beyond the image is the zero padding
-                const NetCrop& c = ct.c[n];
-                const bool inside = c.ox + x < c.img_w && c.oy + y < c.img_h;
-                float r[4];
-                unsigned short mk[4] = {};
-                if constexpr (MODE == kBwdMasked) {
-                    const uint2 mv = *reinterpret_cast<const uint2*>(mask + pi * kC + o0);
-                    mk[0] = static_cast<unsigned short>(mv.x);
-                    mk[1] = static_cast<unsigned short>(mv.x >> 16);
-                    mk[2] = static_cast<unsigned short>(mv.y);
-                    mk[3] = static_cast<unsigned short>(mv.y >> 16);
-                }
+                const bf16x8 b = __builtin_bit_cast(bf16x8, bits);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float v = acc[m][i];
-                    if constexpr (MODE == kFwdRelu) {
-                        v = inside ? fmaxf(v + bias[o0 + i], 0.0f) : 0.0f;
-                    } else {  // through the ReLU that produced this layer's input
-                        if (!(bf16_float(mk[i]) > 0.0f)) v = 0.0f;
+                for (int m = 0; m < MT; ++m)
+                    acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[t][m], b, acc[m], 0, 0, 0);
+            }
+            // lane holds output channels 16 m + 4 kq + i of pixel xs + row
+            const int x = xs + row;
+            if (x >= cw) continue;
+            const size_t pi = base + static_cast<size_t>(y) * cw + x;
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                const int o0 = m * 16 + kq * 4;
+                if constexpr (MODE == kFwdLogits) {
+                    const NetCrop& c = ct.c[n];
+                    const int ph = ((c.oy + y) % S) * S + (c.ox + x) % S;
+                    f32x4 v;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int o = o0 + i;
+                        v[i] = o < kC3 ? acc[m][i] + bias[o] + P[ph * kC3 + o] : 0.0f;
                     }
-                    r[i] = v;
+                    *reinterpret_cast<f32x4*>(out32 + pi * 16 + o0) = v;
+                } else {
+                    // a hidden activation beyond the image is the zero padding
+                    const NetCrop& c = ct.c[n];
+                    const bool inside = c.ox + x < c.img_w && c.oy + y < c.img_h;
+                    float r[4];
+                    unsigned short mk[4] = {};
+                    if constexpr (MODE == kBwdMasked) {
+                        const uint2 mv = *reinterpret_cast<const uint2*>(mask + pi * kC + o0);
+                        mk[0] = static_cast<unsigned short>(mv.x);
+                        mk[1] = static_cast<unsigned short>(mv.x >> 16);
+                        mk[2] = static_cast<unsigned short>(mv.y);
+                        mk[3] = static_cast<unsigned short>(mv.y >> 16);
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        float v = acc[m][i];
+                        if constexpr (MODE == kFwdRelu) {
+                            v = inside ? fmaxf(v + bias[o0 + i], 0.0f) : 0.0f;
+                        } else {  // through the ReLU that produced this layer's input
+                            if (!(bf16_float(mk[i]) > 0.0f)) v = 0.0f;
+                        }
+                        r[i] = v;
+                    }
+                    *reinterpret_cast<uint2*>(out16 + pi * kC + o0) =
+                        make_uint2(pack2(r[0], r[1]), pack2(r[2], r[3]));
                 }
-                *reinterpret_cast<uint2*>(out16 + pi * kC + o0) =
-                    make_uint2(pack2(r[0], r[1]), pack2(r[2], r[3]));
             }
         }
     }
@@ -262,7 +273,7 @@ __global__ __launch_bounds__(256) void conv_kernel(
 // of dz3 are taken in fixed point, rint(d * 2^18) in int32 (a workgroup's
 // kLossPx pixels stay below 2^31), so they do not depend on the order of
 // the LDS atomics and the gradient is the same on every run.
-constexpr int kLossPx = 4096;
+constexpr int kLossPx = 1024;  // four pixels per thread (sixteen left half the units idle: 39 us)
 constexpr float kLossQ = 262144.0f;  // 2^18
 
 __global__ __launch_bounds__(256) void loss_kernel(const float* __restrict__ logits,
@@ -294,13 +305,12 @@ __global__ __launch_bounds__(256) void loss_kernel(const float* __restrict__ log
 #pragma unroll
         for (int j = 0; j < 16; ++j) packed[j] = 0u;
         if (t >= 0 && t < kC3) {
-            float v[kC3];
-            float mx = lg[0];
+            const f32x4 l0 = reinterpret_cast<const f32x4*>(lg)[0];
+            const f32x4 l1 = reinterpret_cast<const f32x4*>(lg)[1];
+            float v[kC3] = {l0.x, l0.y, l0.z, l0.w, l1.x, l1.y, l1.z, l1.w, lg[8]};
+            float mx = v[0];
 #pragma unroll
-            for (int c = 0; c < kC3; ++c) {
-                v[c] = lg[c];
-                mx = fmaxf(mx, v[c]);
-            }
+            for (int c = 0; c < kC3; ++c) mx = fmaxf(mx, v[c]);
             float lt = 0.0f;
 #pragma unroll
             for (int c = 0; c < kC3; ++c) lt = c == t ? v[c] : lt;
@@ -1223,7 +1233,7 @@ hipError_t enqueue_forward(const NetWs& nw, const CropTable& ct, int n, int cw, 
         KernelTimer t("net_input", s);
         input_kernel<<<dim3((per + 255) / 256, n), 256, 0, s>>>(ct, cw, ch, nw.x);
     }
-    const dim3 grid((cw + kTW - 1) / kTW, (ch + kTRows - 1) / kTRows, n);
+    const dim3 grid((cw + kTW - 1) / kTW, (ch + kTRows * kTSteps - 1) / (kTRows * kTSteps), n);
     {
         KernelTimer t("net_conv1", s);
         conv_kernel<2, kFwdRelu, kXC><<<grid, 256, 0, s>>>(nw.x, nw.wt.W1b, params + kOffB1,
@@ -1253,7 +1263,7 @@ hipError_t enqueue_backward(const NetWs& nw, const CropTable& ct, int n, int cw,
             nw.logits, target, ct, S, cw, ch, total, nw.dz3, nw.part_loss, nw.loss_region, nw.lossp);
     }
     const dim3 ggrid((cw + kGW - 1) / kGW, (ch + kGStrip - 1) / kGStrip, n);
-    const dim3 cgrid((cw + kTW - 1) / kTW, (ch + kTRows - 1) / kTRows, n);
+    const dim3 cgrid((cw + kTW - 1) / kTW, (ch + kTRows * kTSteps - 1) / (kTRows * kTSteps), n);
     {
         KernelTimer t("net_wgrad3", s);
         wgrad_kernel<1, kC><<<ggrid, kGThreads, 0, s>>>(nw.dz3, nw.a2, cw, ch, kC3, kC, 0, nw.part_w3,
