@@ -24,9 +24,11 @@
 // chosen pixel's Lab and position; its count and first accumulators are
 // cleared.
 //
-// Each workgroup converts a tile plus a two-pixel halo into LDS, stores the
-// tile, and seeds every cell whose middle pixel lies in the tile: the window
-// and the gradient's neighbours stay within two pixels of that pixel.
+// Each workgroup converts a tile into LDS, stores it, and seeds every cell
+// whose middle pixel lies in the tile: the window and the gradient's
+// neighbours stay within two pixels of that pixel, so of the two-pixel halo
+// only what some seed of the tile reaches is converted (nothing, where the
+// step divides the tile's sides).
 #include <atomic>
 #include <cmath>
 
@@ -132,12 +134,31 @@ __device__ __forceinline__ float cie_f(float t) {
     if (td > eps) return cbrt_rounded(td);
     const double p = kappa * td;
     const double s = p + 16.0;
-    return static_cast<float>(s / 116.0);
+    // s / 116 correctly rounded: the reciprocal's quotient corrected by its
+    // exact remainder (four instructions; the division sequence has twelve)
+    const double rcp = 1.0 / 116.0;
+    const double q0 = s * rcp;
+    return static_cast<float>(__builtin_fma(__builtin_fma(-116.0, q0, s), rcp, q0));
 }
 
-__device__ __forceinline__ void rgb_to_lab(const float* lin, const float* nm, const uint8_t* p,
-                                           float* L, float* A, float* B) {
-    const float r = lin[p[0]], g = lin[p[1]], b = lin[p[2]];
+// Global (device) memory as a named address space: accesses through pointers
+// read from a table would compile to flat instructions, which also count
+// against the LDS wait counter, so every table lookup would wait for them.
+template <class T>
+using gmem = __attribute__((address_space(1))) T;
+
+template <class T>
+__device__ __forceinline__ gmem<T>* as_global(T* p) {
+    return (gmem<T>*)p;
+}
+
+struct Bytes {
+    uint8_t r, g, b;
+};
+
+__device__ __forceinline__ void rgb_to_lab(const float* lin, const float* nm, Bytes p, float* L,
+                                           float* A, float* B) {
+    const float r = lin[p.r], g = lin[p.g], b = lin[p.b];
     float X = nm[0] * r;
     X = X + nm[1] * g;
     X = X + nm[2] * b;
@@ -157,9 +178,9 @@ __device__ __forceinline__ void rgb_to_lab(const float* lin, const float* nm, co
 }
 
 // XYZ scaled by 100 (the colour-space option), in the Lab path's order.
-__device__ __forceinline__ void rgb_to_xyz100(const float* lin, const float* nm, const uint8_t* p,
-                                              float* X0, float* Y0, float* Z0) {
-    const float r = lin[p[0]], g = lin[p[1]], b = lin[p[2]];
+__device__ __forceinline__ void rgb_to_xyz100(const float* lin, const float* nm, Bytes p, float* X0,
+                                              float* Y0, float* Z0) {
+    const float r = lin[p.r], g = lin[p.g], b = lin[p.b];
     float X = nm[0] * r;
     X = X + nm[1] * g;
     X = X + nm[2] * b;
@@ -183,23 +204,23 @@ __device__ __forceinline__ float norm2(float u, float v, float t) {
 
 constexpr int kTW = 64, kTH = 32, kHalo = 2;  // the tile of batches and large frames
 constexpr int kThreads = 1024;
-// Smaller frames: the kernel is bound by its cube roots, so the time is set
-// by the conversions (tile plus halo) of the busiest compute unit.  With
-// 64 x 32 tiles a 320 x 240 frame keeps 40 units busy and a 640 x 480 frame
-// 150; the smallest tile whose count still fits one workgroup per unit
-// spreads the work: 32 x 16 (720 conversions each) or 40 x 30 (1,496; 256
-// tiles at 640 x 480), else 64 x 32 (2,448), whose halo costs least when
-// every unit gets several tiles.  (32 x 16 tiles at 640 x 480, three per
-// unit, were slower than 64 x 32.)
+// Smaller frames take 32 x 16 tiles, one pixel per thread: the time follows
+// the conversions of the busiest compute unit, and small tiles spread them.
 constexpr int kSmallTW = 32, kSmallTH = 16, kSmallThreads = 512;
-constexpr int kMidTW = 40, kMidTH = 30;
 
 // kBatch: the workgroup's image comes from the tile map (a batch) rather
 // than the kernel argument; separate instantiations, so a single-image
 // launch reads no table and takes no branch on the way in.  TW x TH: the
 // tile (plus a kHalo ring), NT threads.
+// What bounds it: the FP64 arithmetic of the cube roots, some 150 vector
+// instructions per pixel.  Converting the whole halo was a fifth of them, in a
+// third pass of the 64 x 32 tile's threads; without it the 64-image batch
+// (54.8 Mpix) takes 370 us instead of 475, 1920 x 1080 21.0 instead of 22.8,
+// 320 x 240 4.2 instead of 5.0.  Held to 80 SGPRs: with more, a SIMD holds
+// seven waves (the trap handler's 16 count too), so a compute unit only one
+// workgroup of 16 waves instead of two (590 us).
 template <bool kBatch, int TW, int TH, int NT>
-__global__ __launch_bounds__(NT) void lab_seed_kernel(LabSeedImage single, LabSeedTileMap map,
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_num_sgpr(80))) void lab_seed_kernel(LabSeedImage single, LabSeedTileMap map,
                                                       LabTables tab) {
     constexpr int kSW = TW + 2 * kHalo, kSH = TH + 2 * kHalo;  // staged tile
     constexpr int kSeedsPerPass = NT / 9;
@@ -227,35 +248,51 @@ __global__ __launch_bounds__(NT) void lab_seed_kernel(LabSeedImage single, LabSe
         bx = blockIdx.x;
         by = blockIdx.y;
     }
-    __syncthreads();
     const int x0 = bx * TW, y0 = by * TH;
 
-    // ---- convert the tile and its halo
-    for (int i = threadIdx.x; i < kSW * kSH; i += NT) {
-        const int x = x0 - kHalo + i % kSW, y = y0 - kHalo + i / kSW;
-        if (x < 0 || y < 0 || x >= g.w || y >= g.h) continue;
-        float l, a, b;
-        const uint8_t* px = g.rgb + static_cast<size_t>(y) * g.pitch + static_cast<size_t>(x) * g.channels;
-        if (g.space == 0) {
-            rgb_to_lab(lin, tab.nm, px, &l, &a, &b);
-        } else if (g.space == 1) {
-            rgb_to_xyz100(lin, tab.nm, px, &l, &a, &b);
-        } else {
-            l = static_cast<float>(px[0]);
-            a = static_cast<float>(px[1]);
-            b = static_cast<float>(px[2]);
-        }
-        sL[i] = l;
-        sA[i] = a;
-        sB[i] = b;
-        if (x >= x0 && x < x0 + TW && y >= y0 && y < y0 + TH) {
-            const size_t pi = static_cast<size_t>(y) * g.w + x;
-            g.L[pi] = l;
-            g.A[pi] = a;
-            g.B[pi] = b;
-        }
+    // ---- the tile's pixels, every load first (from a clamped position)
+    constexpr int kPer = TW * TH / NT;
+    static_assert(kPer * NT == TW * TH, "whole pixels per thread");
+    auto load = [&](int x, int y) {
+        gmem<const uint8_t>* const p = as_global(g.rgb) + static_cast<size_t>(y) * g.pitch +
+                                       static_cast<size_t>(x) * g.channels;
+        return Bytes{p[0], p[1], p[2]};
+    };
+    Bytes px[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int i = threadIdx.x + u * NT;
+        px[u] = load(min(x0 + i % TW, g.w - 1), min(y0 + i / TW, g.h - 1));
     }
     __syncthreads();
+    // planes of one pixel into LDS entry si
+    auto convert = [&](Bytes p, int si, float* l, float* a, float* b) {
+        if (g.space == 0) {
+            rgb_to_lab(lin, tab.nm, p, l, a, b);
+        } else if (g.space == 1) {
+            rgb_to_xyz100(lin, tab.nm, p, l, a, b);
+        } else {
+            *l = static_cast<float>(p.r);
+            *a = static_cast<float>(p.g);
+            *b = static_cast<float>(p.b);
+        }
+        sL[si] = *l;
+        sA[si] = *a;
+        sB[si] = *b;
+    };
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int i = threadIdx.x + u * NT;
+        const int tx = i % TW, ty = i / TW;
+        float l, a, b;
+        convert(px[u], (ty + kHalo) * kSW + tx + kHalo, &l, &a, &b);
+        if (x0 + tx < g.w && y0 + ty < g.h) {
+            const size_t pi = static_cast<size_t>(y0 + ty) * g.w + x0 + tx;
+            as_global(g.L)[pi] = l;
+            as_global(g.A)[pi] = a;
+            as_global(g.B)[pi] = b;
+        }
+    }
 
     // ---- cells whose middle pixel lies in this tile
     const int S = g.S;
@@ -263,14 +300,28 @@ __global__ __launch_bounds__(NT) void lab_seed_kernel(LabSeedImage single, LabSe
         const int lo = c * S, hi = min(lo + S, extent);
         return lo + (hi - lo - 1) / 2;
     };
-    int cx0 = x0 / S, cx1 = min((x0 + TW - 1) / S, g.ns_c - 1);
+    int cx0 = g.by_S.quotient(x0), cx1 = min(g.by_S.quotient(x0 + TW - 1), g.ns_c - 1);
     if (middle(cx0, g.w) < x0) ++cx0;
     if (cx1 >= cx0 && middle(cx1, g.w) >= x0 + TW) --cx1;
-    int cy0 = y0 / S, cy1 = min((y0 + TH - 1) / S, g.ns_r - 1);
+    int cy0 = g.by_S.quotient(y0), cy1 = min(g.by_S.quotient(y0 + TH - 1), g.ns_r - 1);
     if (middle(cy0, g.h) < y0) ++cy0;
     if (cy1 >= cy0 && middle(cy1, g.h) >= y0 + TH) --cy1;
     const int ncx = cx1 - cx0 + 1, ncy = cy1 - cy0 + 1;
     if (ncx <= 0 || ncy <= 0) return;  // uniform across the workgroup
+    // the halo that the seeds' windows reach
+    const int hx0 = max(middle(cx0, g.w) - 2, 0), hx1 = min(middle(cx1, g.w) + 2, g.w - 1);
+    const int hy0 = max(middle(cy0, g.h) - 2, 0), hy1 = min(middle(cy1, g.h) + 2, g.h - 1);
+    if (g.perturb && (hx0 < x0 || hx1 >= x0 + TW || hy0 < y0 || hy1 >= y0 + TH)) {
+        for (int i = threadIdx.x; i < kSW * kSH; i += NT) {
+            const int x = x0 - kHalo + i % kSW, y = y0 - kHalo + i / kSW;
+            if (x >= x0 && x < x0 + TW && y >= y0 && y < y0 + TH) continue;
+            if (x < hx0 || x > hx1 || y < hy0 || y > hy1) continue;
+            float l, a, b;
+            convert(load(x, y), i, &l, &a, &b);
+        }
+    }
+    __syncthreads();
+
     const int nseeds = ncx * ncy;
     auto at = [&](int x, int y) { return (y - y0 + kHalo) * kSW + (x - x0 + kHalo); };
     for (int base = 0; base < nseeds; base += kSeedsPerPass) {
@@ -311,11 +362,13 @@ __global__ __launch_bounds__(NT) void lab_seed_kernel(LabSeedImage single, LabSe
             }
             const int k = cy * g.ns_c + cx;
             const int i = at(bx, by);
-            float4* c = reinterpret_cast<float4*>(g.cen + static_cast<size_t>(k) * kCenStride);
-            c[0] = make_float4(sL[i], sA[i], sB[i], static_cast<float>(bx));
-            c[1] = make_float4(static_cast<float>(by), 0.0f, 0.0f, 0.0f);
-            g.counts[k] = 0;
-            long long* z = g.sums + static_cast<size_t>(k) * kSumStride;
+            typedef float vf4 __attribute__((ext_vector_type(4)));
+            gmem<vf4>* const c =
+                reinterpret_cast<gmem<vf4>*>(as_global(g.cen) + static_cast<size_t>(k) * kCenStride);
+            c[0] = vf4{sL[i], sA[i], sB[i], static_cast<float>(bx)};
+            c[1] = vf4{static_cast<float>(by), 0.0f, 0.0f, 0.0f};
+            as_global(g.counts)[k] = 0;
+            gmem<long long>* const z = as_global(g.sums) + static_cast<size_t>(k) * kSumStride;
 #pragma unroll
             for (int j = 0; j < kSumStride; ++j) z[j] = 0;
         }
@@ -345,6 +398,7 @@ LabSeedImage lab_seed_image(const uint8_t* rgb, int32_t w, int32_t h, int32_t pi
     a.A = ws.A;
     a.B = ws.B;
     a.S = grid.S;
+    a.by_S = make_divisor(grid.S);
     a.ns_c = grid.ns_c;
     a.ns_r = grid.ns_r;
     a.perturb = perturb;
@@ -379,15 +433,10 @@ hipError_t launch_lab_seed(const uint8_t* rgb, int32_t w, int32_t h, int32_t pit
     a.n_clear = clear ? static_cast<uint32_t>(n_clear / 4) : 0;  // (words: a multiple of 4)
     const LabSeedTileMap none{nullptr, nullptr, nullptr};
     KernelTimer t("lab_seed", s);
-    const int cus = compute_units();
-    auto tiles = [&](int tw, int th) { return ((w + tw - 1) / tw) * ((h + th - 1) / th); };
-    if (tiles(kSmallTW, kSmallTH) <= cus) {
-        dim3 g((w + kSmallTW - 1) / kSmallTW, (h + kSmallTH - 1) / kSmallTH);
+    const int small_x = (w + kSmallTW - 1) / kSmallTW, small_y = (h + kSmallTH - 1) / kSmallTH;
+    if (static_cast<long long>(small_x) * small_y <= 4ll * compute_units()) {
         lab_seed_kernel<false, kSmallTW, kSmallTH, kSmallThreads>
-            <<<g, kSmallThreads, 0, s>>>(a, none, tables());
-    } else if (tiles(kMidTW, kMidTH) <= cus) {
-        dim3 g((w + kMidTW - 1) / kMidTW, (h + kMidTH - 1) / kMidTH);
-        lab_seed_kernel<false, kMidTW, kMidTH, kThreads><<<g, kThreads, 0, s>>>(a, none, tables());
+            <<<dim3(small_x, small_y), kSmallThreads, 0, s>>>(a, none, tables());
     } else {
         dim3 g((w + kTW - 1) / kTW, (h + kTH - 1) / kTH);
         lab_seed_kernel<false, kTW, kTH, kThreads><<<g, kThreads, 0, s>>>(a, none, tables());

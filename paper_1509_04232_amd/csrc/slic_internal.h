@@ -77,6 +77,7 @@ struct LabSeedImage {
     int w, h, pitch, channels;
     float *L, *A, *B;
     int S, ns_c, ns_r, perturb, space;
+    Divisor by_S;
     float* cen;
     int32_t* counts;
     long long* sums;  // first accumulator buffer
