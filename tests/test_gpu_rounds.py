@@ -119,3 +119,20 @@ def test_frames_beside_other_kernels(slic):
     torch.cuda.synchronize()
     for i, lb in outs:
         assert np.array_equal(lb.cpu().numpy(), want[i]["labels"])
+
+
+@pytest.mark.parametrize("w,h", [(1, 1), (1, 40), (63, 17), (65, 15), (130, 33), (5, 70000)])
+def test_stray_filter_and_energy_at_tile_edges(slic, w, h):
+    rng = np.random.default_rng(w * 131 + h)
+    img = rng.integers(0, 256, (h, w, 3), dtype=np.uint8)
+    S = 5
+    want = oracle.segment(img, S, 5.0, 2, True, False)
+    ctx = slic.Context(slic.Params(w, h, S=S, m=5.0), _gpu(img))
+    ctx.iterate(2)
+    e = ctx.energy()
+    ctx.filter_stray(3)
+    lb = ctx.labels()
+    torch.cuda.synchronize()
+    assert float(e.cpu()[0]) == pytest.approx(want["energy"], rel=1e-9)
+    assert np.array_equal(lb.cpu().numpy(), oracle.stray_filter(want["labels"], 3))
+    ctx.close()
