@@ -622,12 +622,11 @@ int slic_init_from_centres(slic_ctx** out, const slic_params* p, const uint8_t* 
     if (!c) return SLIC_ENOMEM;
     bind(c, p, d_ws, hip_stream);
     const slic_params& q = c->p;
-    // the conversion kernel also seeds (and clears the counts and first
-    // accumulators); the given centres then replace the seeds
+    // the conversion kernel takes the given centres in place of the seeds
     hipError_t e = hipGetDevice(&c->device);
     if (e == hipSuccess)
-        e = launch_lab_seed(d_rgb, q.width, q.height, q.pitch, q.channels, c->ws, c->g, 0, c->stream);
-    if (e == hipSuccess) e = launch_import_centres(c->ws, c->g, d_centres, c->stream);
+        e = launch_lab_seed(d_rgb, q.width, q.height, q.pitch, q.channels, c->ws, c->g, 0, c->stream,
+                            nullptr, 0, d_centres);
     if (e == hipSuccess) {
         c->t = 0;
         e = launch_assign(c->ws, q.width, q.height, c->g, c->t, c->variant, c->stream);

@@ -365,8 +365,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_num_sgpr(80))) void lab_s
             typedef float vf4 __attribute__((ext_vector_type(4)));
             gmem<vf4>* const c =
                 reinterpret_cast<gmem<vf4>*>(as_global(g.cen) + static_cast<size_t>(k) * kCenStride);
-            c[0] = vf4{sL[i], sA[i], sB[i], static_cast<float>(bx)};
-            c[1] = vf4{static_cast<float>(by), 0.0f, 0.0f, 0.0f};
+            if (!kBatch && g.given) {  // the caller's centre takes the seed's place
+                gmem<const float>* const q = as_global(g.given) + static_cast<size_t>(k) * 5;
+                c[0] = vf4{q[0], q[1], q[2], q[3]};
+                c[1] = vf4{q[4], 0.0f, 0.0f, 0.0f};
+            } else {
+                c[0] = vf4{sL[i], sA[i], sB[i], static_cast<float>(bx)};
+                c[1] = vf4{static_cast<float>(by), 0.0f, 0.0f, 0.0f};
+            }
             as_global(g.counts)[k] = 0;
             gmem<long long>* const z = as_global(g.sums) + static_cast<size_t>(k) * kSumStride;
 #pragma unroll
@@ -407,6 +413,7 @@ LabSeedImage lab_seed_image(const uint8_t* rgb, int32_t w, int32_t h, int32_t pi
     a.counts = ws.counts;
     a.sums = ws.sums;
     a.tiles_x = (w + kTW - 1) / kTW;
+    a.given = nullptr;
     a.clear = nullptr;
     a.n_clear = 0;
     return a;
@@ -427,8 +434,9 @@ int compute_units() {
 
 hipError_t launch_lab_seed(const uint8_t* rgb, int32_t w, int32_t h, int32_t pitch,
                            int32_t channels, const Workspace& ws, const Grid& grid, int perturb,
-                           hipStream_t s, uint32_t* clear, size_t n_clear) {
+                           hipStream_t s, uint32_t* clear, size_t n_clear, const float* given) {
     LabSeedImage a = lab_seed_image(rgb, w, h, pitch, channels, ws, grid, perturb);
+    a.given = given;
     a.clear = reinterpret_cast<uint4*>(clear);
     a.n_clear = clear ? static_cast<uint32_t>(n_clear / 4) : 0;  // (words: a multiple of 4)
     const LabSeedTileMap none{nullptr, nullptr, nullptr};

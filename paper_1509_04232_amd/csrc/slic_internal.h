@@ -82,6 +82,7 @@ struct LabSeedImage {
     int32_t* counts;
     long long* sums;  // first accumulator buffer
     int tiles_x;      // conversion tiles per row
+    const float* given;  // centres float[K][5] in place of the seeds (may be null)
     uint4* clear;  // memory to zero for a launch that follows (16-byte units)
     uint32_t n_clear;
 };
@@ -92,7 +93,8 @@ struct LabSeedTileMap {
 };
 hipError_t launch_lab_seed(const uint8_t* rgb, int32_t w, int32_t h, int32_t pitch,
                            int32_t channels, const Workspace& ws, const Grid& grid, int perturb,
-                           hipStream_t s, uint32_t* clear = nullptr, size_t n_clear = 0);
+                           hipStream_t s, uint32_t* clear = nullptr, size_t n_clear = 0,
+                           const float* given = nullptr);
 // Compute units of the current device.
 int compute_units();
 hipError_t launch_lab_seed_batch(const LabSeedTileMap& map, int total_tiles, hipStream_t s);
@@ -233,9 +235,6 @@ hipError_t launch_stray_filter(const Workspace& ws, int32_t w, int32_t h, int32_
 // cleared, so that association launch 1 starts from them.
 hipError_t launch_import_labels(const Workspace& ws, int32_t w, int32_t h, const Grid& g,
                                 const int32_t* given, hipStream_t s);
-// Centres float[K][5] from the caller into the workspace (stride kCenStride).
-hipError_t launch_import_centres(const Workspace& ws, const Grid& g, const float* in,
-                                 hipStream_t s);
 hipError_t launch_export_centres(const Workspace& ws, const Grid& g, float* out, int32_t* counts,
                                  hipStream_t s);
 
