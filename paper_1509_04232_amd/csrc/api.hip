@@ -185,13 +185,39 @@ hipError_t associate(slic_ctx* c, bool* ccl, bool store) {
                          store);
 }
 
+// The words that a rounds launch needs zero, for the conversion launch of a
+// context to clear (null: the frame has no rounds launch).
+uint32_t* words_to_clear(slic_ctx* c, size_t* words) {
+    *words = 0;
+    const int tiles = rounds_variant(c->ws, c->p.width, c->p.height, c->g, c->variant, kMinRounds);
+    c->clean = tiles != 0;
+    return tiles ? rounds_clear(c->ws, c->p.width, c->p.height, c->g, tiles, words) : nullptr;
+}
+
+// Whether those words are still zero, for the launch about to use them.  A
+// captured launch clears them itself: it may be replayed without the
+// conversion.
+bool take_clean(slic_ctx* c) {
+    const bool clean = c->clean;
+    c->clean = false;
+    if (!clean) return false;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return cap == hipStreamCaptureStatusNone;
+}
+
 // Section 4's listing up to the first association (ccl, store: as in
 // associate, for a first association that is also the last, or that rounds
 // follow at once).
 hipError_t enqueue_init(slic_ctx* c, const uint8_t* rgb, bool* ccl = nullptr, bool store = true) {
     const slic_params& p = c->p;
+    size_t words;
+    uint32_t* const clear = words_to_clear(c, &words);
     hipError_t e = launch_lab_seed(rgb, p.width, p.height, p.pitch, p.channels, c->ws, c->g,
-                                   (p.flags & SLIC_PERTURB_SEEDS) ? 1 : 0, c->stream);
+                                   (p.flags & SLIC_PERTURB_SEEDS) ? 1 : 0, c->stream, clear, words);
     if (e != hipSuccess) return e;
     c->t = 0;
     e = associate(c, ccl, store);
@@ -203,15 +229,15 @@ hipError_t enqueue_init(slic_ctx* c, const uint8_t* rgb, bool* ccl = nullptr, bo
 // the previous launch's centre update (ccl: as in associate, for the last
 // of them; untouched when n is 0).  Only the last launch writes the labels.
 // Where the frame suits it, one launch runs all rounds (all but the last with
-// *ccl, whose launch has tiles of its own).  cleared: as in launch_rounds.
-hipError_t enqueue_iterations(slic_ctx* c, int32_t n, bool* ccl = nullptr, bool cleared = false) {
+// *ccl, whose launch has tiles of its own).
+hipError_t enqueue_iterations(slic_ctx* c, int32_t n, bool* ccl = nullptr) {
     const bool tail = ccl && *ccl;
     const int32_t together = n - (tail ? 1 : 0);
     int32_t i = 0;
     const int tiles = rounds_variant(c->ws, c->p.width, c->p.height, c->g, c->variant, together);
     if (tiles) {
         const hipError_t e = launch_rounds(c->ws, c->p.width, c->p.height, c->g, c->t, together,
-                                           tiles, !tail, true, cleared, c->stream);
+                                           tiles, !tail, true, take_clean(c), c->stream);
         if (e != hipSuccess) return e;
         c->t += together;
         i = together;
@@ -251,6 +277,7 @@ void bind(slic_ctx* c, const slic_params* p, void* d_ws, void* stream) {
     c->state = 0;
     c->variant = resolve_variant(p->width, p->height, c->g.S);
     c->t = 0;
+    c->clean = false;
     c->device = 0;
 }
 
@@ -624,9 +651,12 @@ int slic_init_from_centres(slic_ctx** out, const slic_params* p, const uint8_t* 
     const slic_params& q = c->p;
     // the conversion kernel takes the given centres in place of the seeds
     hipError_t e = hipGetDevice(&c->device);
-    if (e == hipSuccess)
+    if (e == hipSuccess) {
+        size_t words;
+        uint32_t* const clear = words_to_clear(c, &words);
         e = launch_lab_seed(d_rgb, q.width, q.height, q.pitch, q.channels, c->ws, c->g, 0, c->stream,
-                            nullptr, 0, d_centres);
+                            clear, words, d_centres);
+    }
     if (e == hipSuccess) {
         c->t = 0;
         e = launch_assign(c->ws, q.width, q.height, c->g, c->t, c->variant, c->stream);
@@ -656,9 +686,12 @@ int slic_init_from_labels(slic_ctx** out, const slic_params* p, const uint8_t* d
     // conversion and seeding (which clears the first accumulators), then the
     // given labels as association launch 0
     hipError_t e = hipGetDevice(&c->device);
-    if (e == hipSuccess)
+    if (e == hipSuccess) {
+        size_t words;
+        uint32_t* const clear = words_to_clear(c, &words);
         e = launch_lab_seed(d_rgb, q.width, q.height, q.pitch, q.channels, c->ws, c->g,
-                            (q.flags & SLIC_PERTURB_SEEDS) ? 1 : 0, c->stream);
+                            (q.flags & SLIC_PERTURB_SEEDS) ? 1 : 0, c->stream, clear, words);
+    }
     if (e == hipSuccess) e = launch_import_labels(c->ws, q.width, q.height, c->g, d_labels0, c->stream);
     if (e != hipSuccess) {
         delete c;
@@ -683,7 +716,19 @@ int slic_iterate_converge(slic_ctx* c, int32_t max_iters, float threshold,
     if (c->state != 0) return SLIC_ESTATE;
     const double q = std::ldexp(static_cast<double>(threshold), kQShift);
     if (q * static_cast<double>(c->g.K) > 4.0e18) return SLIC_EINVAL;
-    const Converge cv{c->ws.ctl, std::llrint(q) * static_cast<long long>(c->g.K), c->t};
+    const long long limit = std::llrint(q) * static_cast<long long>(c->g.K);
+    const int tiles =
+        rounds_variant(c->ws, c->p.width, c->p.height, c->g, c->variant, max_iters);
+    if (tiles) {
+        const RoundsStop stop{limit, d_iters_done};
+        if (launch_rounds(c->ws, c->p.width, c->p.height, c->g, c->t, max_iters, tiles, true, false,
+                          take_clean(c), c->stream, &stop) != hipSuccess)
+            return fail(c);
+        c->t += max_iters;
+        c->state = 3;
+        return SLIC_OK;
+    }
+    const Converge cv{c->ws.ctl, limit, c->t};
     if (launch_converge_reset(c->ws.ctl, c->stream) != hipSuccess) return fail(c);
     for (int32_t i = 0; i < max_iters; ++i) {
         if (launch_assign(c->ws, c->p.width, c->p.height, c->g, c->t, c->variant, c->stream, &cv) !=
@@ -790,11 +835,10 @@ namespace {
 // whether the decoded labels are written; rounds that follow at once make
 // them dead).
 hipError_t enqueue_warm_init(slic_ctx* c, const uint8_t* rgb, const void* d_net,
-                             bool store = true, int tiles = 0) {
+                             bool store = true) {
     const slic_params& p = c->p;
-    size_t words = 0;
-    uint32_t* const to_clear =
-        tiles ? rounds_clear(c->ws, p.width, p.height, c->g, tiles, &words) : nullptr;
+    size_t words;
+    uint32_t* const to_clear = words_to_clear(c, &words);
     hipError_t e = launch_lab_seed(rgb, p.width, p.height, p.pitch, p.channels, c->ws, c->g,
                                    (p.flags & SLIC_PERTURB_SEEDS) ? 1 : 0, c->stream, to_clear, words);
     if (e != hipSuccess) return e;
@@ -859,10 +903,8 @@ int slic_warm_segment(const slic_params* p, const uint8_t* d_rgb, const void* d_
     c.ws.labels = d_labels;
     // with rounds, the last association also finds the tile-local components
     bool local_done = enforce != 0 && n_iters > 0;
-    const int tiles = rounds_variant(c.ws, p->width, p->height, c.g, c.variant,
-                                     n_iters - (local_done ? 1 : 0));
-    if (enqueue_warm_init(&c, d_rgb, d_net, n_iters == 0, tiles) != hipSuccess) return SLIC_EHIP;
-    if (enqueue_iterations(&c, n_iters, &local_done, tiles != 0) != hipSuccess) return SLIC_EHIP;
+    if (enqueue_warm_init(&c, d_rgb, d_net, n_iters == 0) != hipSuccess) return SLIC_EHIP;
+    if (enqueue_iterations(&c, n_iters, &local_done) != hipSuccess) return SLIC_EHIP;
     if (d_energy &&
         launch_energy(c.ws, p->width, p->height, c.g, d_energy, c.stream) != hipSuccess)
         return SLIC_EHIP;

@@ -23,6 +23,11 @@
 // words of round t - 1 from each of them, which they store after they have
 // read (who reads whom is symmetric: own cells at most two apart).
 //
+// Convergence stop: each tile also stores the shift of the centres it owns, as
+// it stages them, in a word that carries the round; before the next round
+// every workgroup adds up all tiles' words (stored half a round before) and
+// takes the same decision.
+//
 // Why every wait ends.  The launch does not assume that all its workgroups
 // run at once.  Each workgroup registers (a bit in a census word) before its
 // first store.  After its first tile it looks until every workgroup has
@@ -73,6 +78,9 @@ struct RoundsArgs {
     int store_last;   // the last round stores the labels
     int sums_last;    // the last round adds its sums to the ring
     int census_ticks;
+    long long limit;     // convergence stop: after a round whose shift is below it
+    unsigned long long* shift;  // two buffers of n_tiles words, zero before the launch
+    int32_t* rounds_run;        // with converge (may be null)
 };
 
 template <class T>
@@ -123,13 +131,14 @@ __device__ __forceinline__ void take_census(const RoundsArgs& a, unsigned* words
 }
 
 // SRC: most tiles that a cell's sums are read from.
-template <int VEC, int ROWS, int DIST, int SRC>
+template <int VEC, int ROWS, int DIST, int SRC, bool kConv>
 __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
     using Sh = Shape<VEC, ROWS>;
     constexpr int kLogW = __builtin_ctz(Sh::kTileW), kLogH = __builtin_ctz(Sh::kTileH);
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ unsigned s_words[64];
     __shared__ int s_late;
+    __shared__ unsigned long long s_shift, s_total[kThreads / 64];
     const AssignImage& g = a.g;
     const int S = g.S;
     const int me = blockIdx.x;
@@ -230,6 +239,7 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
             as_global(a.census) + (me / kCensusBits) * kCensusStride, 1ull << (me % kCensusBits),
             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         s_late = (v & kFrozen) != 0;
+        s_shift = 0;
     }
     load_centre();
     __syncthreads();
@@ -242,7 +252,32 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
     int n_here = 0, my_place = 0;
     int T = me;
     int round = 0;  // association a.t0 + round
+    int checked = 0;  // rounds whose shift has been looked at
     for (bool first = true;; first = false) {
+        if constexpr (kConv) {
+            if (round > checked) {
+                // the shift of the round before, from all tiles
+                gmem<const unsigned long long>* const in =
+                    as_global(static_cast<const unsigned long long*>(a.shift)) +
+                    ((round & 1) ? 0 : a.n_tiles);
+                unsigned long long mine = 0;
+                for (int j = threadIdx.x; j < a.n_tiles; j += kThreads) {
+                    unsigned long long v;
+                    while ((v = agent_load<unsigned long long>(in + j)) >> (32 + kTagShift) !=
+                           static_cast<unsigned>(round)) {
+                    }
+                    mine += v & ((1ull << (32 + kTagShift)) - 1);
+                }
+                for (int d = 32; d > 0; d >>= 1) mine += __shfl_xor(mine, d);
+                if ((threadIdx.x & 63) == 0) s_total[threadIdx.x >> 6] = mine;
+                __syncthreads();
+                unsigned long long total = 0;
+#pragma unroll
+                for (int q = 0; q < kThreads / 64; ++q) total += s_total[q];
+                if (static_cast<long long>(total) < a.limit) break;
+                checked = round;
+            }
+        }
         const long long t = a.t0 + round;
         float4* const cen4 = reinterpret_cast<float4*>(smem);
         float* const cenf = reinterpret_cast<float*>(smem);
@@ -301,6 +336,16 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
             const double q0 = static_cast<double>(s0) / dn;
             const double q1 = static_cast<double>(s1) / dn;
             // a centre with no pixels keeps its value
+            if constexpr (kConv) {  // L1 shift, each component rint(|d| 2^18)
+                if (owner && n > 0) {
+                    const double q = static_cast<double>(1 << kQShift);
+                    const float m0 = static_cast<float>(comp < 3 ? q0 * inv : q0);
+                    long long d = llrint(fabs(static_cast<double>(m0) - v0) * q);
+                    if (comp == 3)
+                        d += llrint(fabs(static_cast<double>(static_cast<float>(q1)) - v1) * q);
+                    if (d) atomicAdd(&s_shift, static_cast<unsigned long long>(d));
+                }
+            }
             v0 = n > 0 ? static_cast<float>(comp < 3 ? q0 * inv : q0) : v0;
             v1 = n > 0 ? static_cast<float>(q1) : v1;
             // where there is no centre, an infinite colour distance never wins
@@ -315,7 +360,7 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
                     agent_store<float>(c + comp, v0);
                     if (comp == 3) agent_store<float>(c + 4, v1);
                 }
-                if (last && t > 0 && comp == 3) as_global(g.counts)[k] = static_cast<int32_t>(n);
+                if ((kConv || last) && t > 0 && comp == 3) as_global(g.counts)[k] = static_cast<int32_t>(n);
                 if (a.sums_last && round >= a.n - 2) {
                     // the ring's accumulators of the last round and of the
                     // launch after it
@@ -329,6 +374,14 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
         if (sums_out)
             for (int j = threadIdx.x; j < kCopies * bin_stride(ncells); j += kThreads) bins[j] = 0ull;
         __syncthreads();
+        if constexpr (kConv) {
+            if (threadIdx.x == 0) {  // (the next additions are two barriers away)
+                agent_store<unsigned long long>(
+                    as_global(a.shift) + ((round & 1) ? a.n_tiles : 0) + T,
+                    s_shift | (static_cast<unsigned long long>(round + 1) << (32 + kTagShift)));
+                s_shift = 0;
+            }
+        }
 
         // ---- associate, labels, sums
         const int x = x0 + tx * VEC, yb = y0 + ty * ROWS;
@@ -336,7 +389,7 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
         const int gx_rel = g.by_S.quotient(col_ok ? x : x0) - gx_lo - 1;
         int cellv[ROWS][VEC];
         find_cells<VEC, ROWS, DIST>(cen4, ceny, kidx, ncx, gx_rel, gy_lo, g, x, yb, pl, pa, pb, cellv);
-        if (last && a.store_last) {
+        if ((kConv || last) && a.store_last) {  // any round may turn out the last
             gmem<int32_t>* const labels = as_global(g.labels);
 #pragma unroll
             for (int r = 0; r < ROWS; ++r) {
@@ -434,6 +487,9 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
         if (!mine) break;
         enter(T);
     }
+    if constexpr (kConv) {
+        if (my_place == 0 && threadIdx.x == 0 && a.rounds_run) *a.rounds_run = min(round, a.n);
+    }
 }
 
 __global__ __launch_bounds__(256) void clear_words_kernel(uint4* p, size_t n) {
@@ -441,40 +497,45 @@ __global__ __launch_bounds__(256) void clear_words_kernel(uint4* p, size_t n) {
     if (i < n) p[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
-template <int VEC, int ROWS, int DIST, int SRC>
+template <int VEC, int ROWS, int DIST, int SRC, bool kConv>
 hipError_t launch_rounds_as(const RoundsArgs& a, hipStream_t s) {
     KernelTimer timer("assign_rounds", s);
-    rounds_kernel<VEC, ROWS, DIST, SRC>
+    rounds_kernel<VEC, ROWS, DIST, SRC, kConv>
         <<<a.n_tiles, kThreads, assign_lds_bytes(kMaxCells, kCopies), s>>>(a);
     return hipGetLastError();
 }
 
 using RoundsFn = hipError_t (*)(const RoundsArgs&, hipStream_t);
 
-// By variant, distance and number of sources.
+// By distance, number of sources and the convergence stop.
 template <int VEC, int ROWS>
-struct ShapeFns {
-    static constexpr RoundsFn fn[2][2] = {
-        {launch_rounds_as<VEC, ROWS, 0, kFewSources>, launch_rounds_as<VEC, ROWS, 0, kMaxSources>},
-        {launch_rounds_as<VEC, ROWS, 1, kFewSources>, launch_rounds_as<VEC, ROWS, 1, kMaxSources>}};
-};
+RoundsFn shape_fn(int dist, int sources, bool conv) {
+    constexpr int F = kFewSources, M = kMaxSources;
+    static constexpr RoundsFn fn[2][2][2] = {
+        {{launch_rounds_as<VEC, ROWS, 0, F, false>, launch_rounds_as<VEC, ROWS, 0, F, true>},
+         {launch_rounds_as<VEC, ROWS, 0, M, false>, launch_rounds_as<VEC, ROWS, 0, M, true>}},
+        {{launch_rounds_as<VEC, ROWS, 1, F, false>, launch_rounds_as<VEC, ROWS, 1, F, true>},
+         {launch_rounds_as<VEC, ROWS, 1, M, false>, launch_rounds_as<VEC, ROWS, 1, M, true>}}};
+    return fn[dist ? 1 : 0][sources > F ? 1 : 0][conv ? 1 : 0];
+}
 
-RoundsFn rounds_fn(int variant, int dist, int sources) {
-    const int d = dist ? 1 : 0, m = sources > kFewSources ? 1 : 0;
+RoundsFn rounds_fn(int variant, int dist, int sources, bool conv) {
     switch (variant) {  // the association's variants, in their order
-        case 1: return ShapeFns<1, 1>::fn[d][m];
-        case 2: return ShapeFns<1, 2>::fn[d][m];
-        case 3: return ShapeFns<1, 4>::fn[d][m];
-        case 4: return ShapeFns<4, 1>::fn[d][m];
-        case 5: return ShapeFns<4, 2>::fn[d][m];
-        case 6: return ShapeFns<2, 1>::fn[d][m];
-        case 7: return ShapeFns<2, 2>::fn[d][m];
+        case 1: return shape_fn<1, 1>(dist, sources, conv);
+        case 2: return shape_fn<1, 2>(dist, sources, conv);
+        case 3: return shape_fn<1, 4>(dist, sources, conv);
+        case 4: return shape_fn<4, 1>(dist, sources, conv);
+        case 5: return shape_fn<4, 2>(dist, sources, conv);
+        case 6: return shape_fn<2, 1>(dist, sources, conv);
+        case 7: return shape_fn<2, 2>(dist, sources, conv);
         default: return nullptr;
     }
 }
 
 size_t clear_words(const RoundsArgs& a) {
-    return (static_cast<size_t>(kMaxWords) * kCensusStride + 2 * a.part_words) * 2;
+    // census, shifts (an even number of words), partial sums
+    return (static_cast<size_t>(kMaxWords) * kCensusStride + 2 * static_cast<size_t>(a.n_tiles) +
+            2 * a.part_words) * 2;
 }
 
 // The launch's arguments for a variant's tiles; false where the frame does
@@ -518,7 +579,8 @@ bool rounds_args(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int v
     // sums lie in the ranks and local roots (adjacent arrays)
     const size_t n = static_cast<size_t>(w) * h * sizeof(int32_t);
     a->census = reinterpret_cast<unsigned long long*>(ws.ccl2);
-    a->part = a->census + kMaxWords * kCensusStride;
+    a->shift = a->census + kMaxWords * kCensusStride;
+    a->part = a->shift + 2 * a->n_tiles;
     return clear_words(*a) * sizeof(uint32_t) <= 2 * n;
 }
 
@@ -555,7 +617,7 @@ uint32_t* rounds_clear(const Workspace& ws, int32_t w, int32_t h, const Grid& g,
 
 hipError_t launch_rounds(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int64_t t0, int n,
                          int variant, bool store_last, bool sums_last, bool cleared, hipStream_t s,
-                         int census_ticks) {
+                         const RoundsStop* stop, int census_ticks) {
     RoundsArgs a;
     int sources = 0;
     if (n < 2 || n > kMaxRounds || !rounds_args(ws, w, h, g, variant, compute_units(), &a, &sources))
@@ -572,7 +634,9 @@ hipError_t launch_rounds(const Workspace& ws, int32_t w, int32_t h, const Grid& 
         clear_words_kernel<<<static_cast<unsigned>((words + 1023) / 1024), 256, 0, s>>>(
             reinterpret_cast<uint4*>(a.census), words / 4);
     }
-    return rounds_fn(variant, g.dist, sources)(a, s);
+    a.limit = stop ? stop->limit : 0;
+    a.rounds_run = stop ? stop->rounds_run : nullptr;
+    return rounds_fn(variant, g.dist, sources, stop != nullptr)(a, s);
 }
 
 }  // namespace slic

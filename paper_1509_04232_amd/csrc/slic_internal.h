@@ -166,13 +166,19 @@ hipError_t launch_assign_final_ccl(const Workspace& ws, int32_t w, int32_t h, co
 // the stream has done so, else the call does.
 // census_ticks: how long a workgroup waits for the others to start, in
 // 10 ns (negative: the built-in time).
+// stop: end after a round whose quantised shift of all centres is below limit,
+// and write the rounds run (device int32, may be null).
 constexpr int kMinRounds = 2;
+struct RoundsStop {
+    long long limit;
+    int32_t* rounds_run;
+};
 int rounds_variant(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int variant, int n);
 uint32_t* rounds_clear(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int variant,
                        size_t* words);
 hipError_t launch_rounds(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int64_t t0, int n,
                          int variant, bool store_last, bool sums_last, bool cleared, hipStream_t s,
-                         int census_ticks = -1);
+                         const RoundsStop* stop = nullptr, int census_ticks = -1);
 hipError_t launch_assign_batch(const AssignTileMap& map, int total_tiles, int min_S, int64_t t,
                                int variant, int dist, hipStream_t s, bool store_labels = true);
 AssignImage assign_image(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int variant);
@@ -278,6 +284,7 @@ struct slic_ctx {
     int device;
     int variant;    // association launch variant
     int64_t t;      // association launches so far
+    bool clean;     // the words of launch_rounds are zero (no launch has used them)
     int state;      // 0: k-means state valid, 1: connectivity done, 2: poisoned,
                     // 3: stopped by the convergence rule (final)
 };

@@ -136,3 +136,26 @@ def test_stray_filter_and_energy_at_tile_edges(slic, w, h):
     assert float(e.cpu()[0]) == pytest.approx(want["energy"], rel=1e-9)
     assert np.array_equal(lb.cpu().numpy(), oracle.stray_filter(want["labels"], 3))
     ctx.close()
+
+
+@pytest.mark.parametrize("squared", [False, True])
+@pytest.mark.parametrize("w,h,S,threshold", [(320, 240, 16, 2.0), (333, 251, 27, 1.0),
+                                             (700, 500, 8, 3.0), (96, 72, 8, 0.0), (640, 480, 16, 1e4)])
+def test_convergence_stop_in_one_launch(slic, squared, w, h, S, threshold):
+    img = _img(w, h, 7 * w + S)
+    ctx = slic.Context(slic.Params(w, h, S=S, m=10.0, squared_distance=squared), _gpu(img))
+    n = ctx.iterate_converge(12, threshold)
+    lb, (cen, cnt) = ctx.labels(), ctx.centres()
+    torch.cuda.synchronize()
+    rounds = int(n.cpu()[0])
+    if squared:  # (the oracle's rule is stated for Eq. 1: the rounds run are taken as given)
+        want = oracle.segment(img, S, 10.0, rounds, True, False, 0, oracle.COLOR_LAB,
+                              oracle.DIST_SQUARED)
+        want = (want["labels"], want["centres"], want["counts"], rounds)
+    else:
+        want = oracle.kmeans_converge(oracle.rgb_to_lab(img), S, 10.0, True, 12, threshold)
+    assert np.array_equal(lb.cpu().numpy(), want[0])
+    assert np.array_equal(cen.cpu().numpy(), want[1])
+    assert np.array_equal(cnt.cpu().numpy(), want[2])
+    assert rounds == want[3]
+    ctx.close()
