@@ -13,6 +13,12 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr unsigned kCertify = 160;  // distance of two keys
+// Infinite distance, the last slot: bounds the second key, so that an
+// infinite or undefined distance is never certified as the best (a given
+// centre may lie so far out that its distances overflow, and with m = 0 its
+// spatial term is then 0 * inf; the cells outside the grid would win).  The
+// keys have no sign, so that an undefined distance comes after an infinite one.
+constexpr unsigned kNoKey = 0x7F80000Fu, kKeyBits = 0x7FFFFFF0u;
 
 // Reference Eq. 1 distance: the exact operation sequence of the definition.
 __device__ __forceinline__ float eq1_reference(float cl, float ca, float cb, float cx, float cy,
@@ -201,7 +207,7 @@ __device__ __forceinline__ void find_eq1(const float4* cen4, const float* ceny, 
                                             : __builtin_fmaf(dy, dy, dx2);
                     const float d = __builtin_fmaf(wgt, __builtin_amdgcn_sqrtf(t),
                                                    __builtin_amdgcn_sqrtf(s));
-                    key[cc][r][v] = (__float_as_uint(d) & ~15u) | static_cast<unsigned>(4 * cr + cc);
+                    key[cc][r][v] = (__float_as_uint(d) & kKeyBits) | static_cast<unsigned>(4 * cr + cc);
                 }
             }
         }
@@ -218,9 +224,9 @@ __device__ __forceinline__ void find_eq1(const float4* cen4, const float* ceny, 
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
             const unsigned best = umin3(lo[0][r][v], lo[1][r][v], lo[2][r][v]);
-            const unsigned second = min(umed3(lo[0][r][v], lo[1][r][v], lo[2][r][v]),
-                                        umin3(mid[0][r][v], mid[1][r][v], mid[2][r][v]));
-            near[r][v] = second - best < kCertify;
+            const unsigned second = umin3(umed3(lo[0][r][v], lo[1][r][v], lo[2][r][v]),
+                                          umin3(mid[0][r][v], mid[1][r][v], mid[2][r][v]), kNoKey);
+            near[r][v] = static_cast<int>(second - best) < static_cast<int>(kCertify);
             cellv[r][v] = base + static_cast<int>((best >> 2) & 3u) * ncx + static_cast<int>(best & 3u);
         }
 }

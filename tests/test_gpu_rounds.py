@@ -159,3 +159,27 @@ def test_convergence_stop_in_one_launch(slic, squared, w, h, S, threshold):
     assert np.array_equal(cnt.cpu().numpy(), want[2])
     assert rounds == want[3]
     ctx.close()
+
+
+@pytest.mark.parametrize("w,h,S,rounds", [(96, 72, 16, 0), (97, 75, 8, 1), (131, 77, 8, 3), (700, 500, 16, 3)])
+def test_given_centres_with_overflowing_distances(slic, w, h, S, rounds):
+    """m = 0 and given centres so far out that their spatial distances
+    overflow: 0 * inf is no distance, and each pixel keeps its own cell (the
+    cells outside the grid are never taken) until the first means."""
+    img = _img(w, h, 3 * w)
+    lab = oracle.rgb_to_lab(img)
+    cen = oracle.kmeans(lab, S, 0.0, True, 0)[1].copy()
+    cen[:, 3] = 1e30
+    p = slic.Params(w, h, S=S, m=0.0)
+    ctx = slic.Context(p, _gpu(img), centres=torch.from_numpy(cen).cuda())
+    labels = (np.arange(h)[:, None] // S) * -(-w // S) + np.arange(w)[None] // S
+    labels = np.ascontiguousarray(labels, dtype=np.int32)
+    for _ in range(rounds):
+        cen, _ = oracle.update(lab, labels, cen)
+        labels = oracle.assign(lab, S, 0.0, cen)
+    ctx.iterate(rounds)
+    lb, (got, _) = ctx.labels(), ctx.centres()
+    torch.cuda.synchronize()
+    assert np.array_equal(lb.cpu().numpy(), labels)
+    assert np.array_equal(got.cpu().numpy(), cen)
+    ctx.close()
