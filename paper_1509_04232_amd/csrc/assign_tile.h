@@ -87,14 +87,42 @@ __device__ __forceinline__ void store_i2(gmem<int32_t>* p, int a, int b) {
     *reinterpret_cast<gmem<vi2>*>(p) = vi2{a, b};
 }
 
+// The squared-sum distance of the SLIC paper the method builds on (an
+// option): d_lab^2 + w^2 d_xy^2 in FP32 in this order, no square roots, so
+// the values compared are the exact ones.
+__device__ __forceinline__ float dist_squared(float cl, float ca, float cb, float cx, float dy2,
+                                              float l, float a, float b, float xf, float wgt) {
+    const float dl = cl - l, da = ca - a, db = cb - b;
+    float s = dl * dl;
+    s = s + da * da;
+    s = s + db * db;
+    const float dx = cx - xf;
+    float t = dx * dx;
+    t = t + dy2;
+    const float w2 = wgt * wgt;
+    const float sp = w2 * t;
+    return s + sp;
+}
+
+// Fast Eq. 1 distance (fused multiply-adds, hardware square root); dy2 is
+// the squared vertical offset, shared by the pixels of a row.
+__device__ __forceinline__ float eq1_fast(float cl, float ca, float cb, float cx, float dy2,
+                                          float l, float a, float b, float xf, float wgt) {
+    const float dl = cl - l, da = ca - a, db = cb - b;
+    const float s = __builtin_fmaf(db, db, __builtin_fmaf(da, da, dl * dl));
+    const float dx = cx - xf;
+    const float t = __builtin_fmaf(dx, dx, dy2);
+    return __builtin_fmaf(wgt, __builtin_amdgcn_sqrtf(t), __builtin_amdgcn_sqrtf(s));
+}
+
 // Reference argmin over the nine candidates of one pixel (near ties only).
 // A cell outside the grid is staged with an infinite colour distance and
 // every distance of a cell inside it is finite (the compactness bound), so
 // the strict test below never selects an outside cell; the pixel's own cell
 // (slot 4) is the starting choice.
 __device__ __forceinline__ int reference_slot(const float4* cen4, const float* ceny, int base,
-                                              int ncx, float l, float a, float b, float xf,
-                                              float yf, float wgt) {
+                                               int ncx, float l, float a, float b, float xf,
+                                               float yf, float wgt) {
     float bref = __builtin_huge_valf();
     int sref = 4;
 #pragma unroll 1
@@ -102,6 +130,27 @@ __device__ __forceinline__ int reference_slot(const float4* cen4, const float* c
         const int li = base + (c / 3) * ncx + (c % 3);
         const float4 q = cen4[li];
         const float d = eq1_reference(q.x, q.y, q.z, q.w, ceny[li], l, a, b, xf, yf, wgt);
+        if (d < bref) {
+            bref = d;
+            sref = c;
+        }
+    }
+    return sref;
+}
+
+// The same under the squared-sum distance, where two keys agree: the lowest
+// distance bits, the lowest slot on ties.
+__device__ __forceinline__ int squared_slot(const float4* cen4, const float* ceny, int base, int ncx,
+                                            float l, float a, float b, float xf, float yf, float wgt) {
+    unsigned bref = ~0u;
+    int sref = 0;
+#pragma unroll 1
+    for (int c = 0; c < 9; ++c) {
+        const int li = base + (c / 3) * ncx + (c % 3);
+        const float4 q = cen4[li];
+        const float dy = ceny[li] - yf;
+        const unsigned d =
+            __float_as_uint(dist_squared(q.x, q.y, q.z, q.w, dy * dy, l, a, b, xf, wgt));
         if (d < bref) {
             bref = d;
             sref = c;
@@ -154,81 +203,56 @@ __device__ __forceinline__ void add_bin(unsigned long long* bins, int ncells, in
     atomicAdd(bins + 3 * ncells + cell, rxyc);
 }
 
-// The squared-sum distance of the SLIC paper the method builds on (an
-// option): d_lab^2 + w^2 d_xy^2 in FP32 in this order, no square roots, so
-// its argmin is taken exactly.
-__device__ __forceinline__ float dist_squared(float cl, float ca, float cb, float cx, float dy2,
-                                              float l, float a, float b, float xf, float wgt) {
-    const float dl = cl - l, da = ca - a, db = cb - b;
-    float s = dl * dl;
-    s = s + da * da;
-    s = s + db * db;
-    const float dx = cx - xf;
-    float t = dx * dx;
-    t = t + dy2;
-    const float w2 = wgt * wgt;
-    const float sp = w2 * t;
-    return s + sp;
-}
-
-// Selection among the nine candidates of NR rows of VEC pixels, all in the
-// cells of window entry `base` (its left upper candidate): the winners' window
-// cells, and where the fast values do not certify the choice.  A candidate is loaded once for all the pixels, its
-// horizontal offsets are shared by the rows and its vertical ones by the
-// columns.
-template <int VEC, int NR>
-__device__ __forceinline__ void find_eq1(const float4* cen4, const float* ceny, int ncx, int base,
-                                         float wgt, int x, int yb, const float (*pl)[VEC],
-                                         const float (*pa)[VEC], const float (*pb)[VEC],
-                                         bool (*near)[VEC], int (*cellv)[VEC]) {
+// Selection among the nine candidates of a row of VEC pixels that lie in one
+// cell (base: its left upper candidate's window entry): the winners' window
+// cells, and where the keys do not settle the choice.  Under Eq. 1 that is
+// where two fast values are too near to certify it; the squared-sum distance
+// is computed exactly, so only where the two smallest agree in all the bits
+// that a key keeps (keys of 32 bits for 64 took 154 instructions per pixel for
+// 189, and a 1080p frame of ten rounds 179 us for 193).  (All rows of a thread against one load of each candidate
+// took 8 instructions per pixel less, and more time: 104 registers for 86.)
+template <int VEC, int DIST>
+__device__ __forceinline__ void find_row(const float4* cen4, const float* ceny, int ncx, int base,
+                                         float wgt, int x, int y, const float (&pl)[VEC],
+                                         const float (&pa)[VEC], const float (&pb)[VEC],
+                                         bool (&near)[VEC], int (&cellv)[VEC]) {
+    const float yf = static_cast<float>(y);
     // the keys of one row of candidates at a time: smallest and middle of
     // three (one instruction each), then of the three rows
-    unsigned lo[3][NR][VEC], mid[3][NR][VEC];
+    unsigned lo[3][VEC], mid[3][VEC];
 #pragma unroll
     for (int cr = 0; cr < 3; ++cr) {
-        unsigned key[3][NR][VEC];
+        unsigned key[3][VEC];
 #pragma unroll
         for (int cc = 0; cc < 3; ++cc) {
             const int li = base + cr * ncx + cc;
             const float4 q = cen4[li];
-            const float qy = ceny[li];
-            float dx[VEC];
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) dx[v] = q.w - static_cast<float>(x + v);
-#pragma unroll
-            for (int r = 0; r < NR; ++r) {
-                const float dy = qy - static_cast<float>(yb + r);
-                const float dy2 = dy * dy, dx2 = dx[0] * dx[0];
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    const float dl = q.x - pl[r][v], da = q.y - pa[r][v], db = q.z - pb[r][v];
-                    const float s = __builtin_fmaf(db, db, __builtin_fmaf(da, da, dl * dl));
-                    const float t = VEC > 1 ? __builtin_fmaf(dx[v], dx[v], dy2)
-                                            : __builtin_fmaf(dy, dy, dx2);
-                    const float d = __builtin_fmaf(wgt, __builtin_amdgcn_sqrtf(t),
-                                                   __builtin_amdgcn_sqrtf(s));
-                    key[cc][r][v] = (__float_as_uint(d) & kKeyBits) | static_cast<unsigned>(4 * cr + cc);
-                }
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < NR; ++r)
+            const float dy = ceny[li] - yf;
+            const float dy2 = dy * dy;
 #pragma unroll
             for (int v = 0; v < VEC; ++v) {
-                lo[cr][r][v] = umin3(key[0][r][v], key[1][r][v], key[2][r][v]);
-                mid[cr][r][v] = umed3(key[0][r][v], key[1][r][v], key[2][r][v]);
+                const float xf = static_cast<float>(x + v);
+                const float d =
+                    DIST == 1 ? dist_squared(q.x, q.y, q.z, q.w, dy2, pl[v], pa[v], pb[v], xf, wgt)
+                              : eq1_fast(q.x, q.y, q.z, q.w, dy2, pl[v], pa[v], pb[v], xf, wgt);
+                key[cc][v] = (__float_as_uint(d) & kKeyBits) | static_cast<unsigned>(4 * cr + cc);
             }
-    }
-#pragma unroll
-    for (int r = 0; r < NR; ++r)
+        }
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
-            const unsigned best = umin3(lo[0][r][v], lo[1][r][v], lo[2][r][v]);
-            const unsigned second = umin3(umed3(lo[0][r][v], lo[1][r][v], lo[2][r][v]),
-                                          umin3(mid[0][r][v], mid[1][r][v], mid[2][r][v]), kNoKey);
-            near[r][v] = static_cast<int>(second - best) < static_cast<int>(kCertify);
-            cellv[r][v] = base + static_cast<int>((best >> 2) & 3u) * ncx + static_cast<int>(best & 3u);
+            lo[cr][v] = umin3(key[0][v], key[1][v], key[2][v]);
+            mid[cr][v] = umed3(key[0][v], key[1][v], key[2][v]);
         }
+    }
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) {
+        const unsigned best = umin3(lo[0][v], lo[1][v], lo[2][v]);
+        const unsigned second = umin3(umed3(lo[0][v], lo[1][v], lo[2][v]),
+                                      umin3(mid[0][v], mid[1][v], mid[2][v]), kNoKey);
+        near[v] = DIST == 1 ? (second ^ best) < 16u
+                            : static_cast<int>(second - best) < static_cast<int>(kCertify);
+        cellv[v] = base + static_cast<int>((best >> 2) & 3u) * ncx + static_cast<int>(best & 3u);
+    }
 }
 
 // The window cell of the centre nearest to each pixel of the thread (rows yb
@@ -245,47 +269,11 @@ __device__ __forceinline__ void find_cells(const float4* cen4, const float* ceny
 #pragma unroll
     for (int r = 0; r < ROWS; ++r)
         rowbase[r] = (g.by_S.quotient(min(yb + r, g.h - 1)) - gy_lo - 1) * ncx + gx_rel;
-    if constexpr (DIST == 1) {
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-            const float yf = static_cast<float>(yb + r);
-            const int base = rowbase[r];
-            // exact: (distance bits, slot) as one 64-bit key, lowest slot on ties
-            unsigned long long bk[VEC];
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) bk[v] = ~0ull;
-#pragma unroll
-            for (int c = 0; c < 9; ++c) {
-                const int li = base + (c / 3) * ncx + (c % 3);
-                const float4 q = cen4[li];
-                const float dy = ceny[li] - yf;
-                const float dy2 = dy * dy;
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    const float d = dist_squared(q.x, q.y, q.z, q.w, dy2, pl[r][v], pa[r][v],
-                                                 pb[r][v], static_cast<float>(x + v), g.wgt);
-                    const unsigned long long key =
-                        (static_cast<unsigned long long>(__float_as_uint(d)) << 4) |
-                        static_cast<unsigned long long>(c);
-                    bk[v] = key < bk[v] ? key : bk[v];
-                }
-            }
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                // an out-of-grid cell (infinite distance) can only come first
-                // when no distance is finite; the own cell is then taken
-                int slot = static_cast<int>(bk[v] & 15ull);
-                const int cell = base + (slot / 3) * ncx + (slot % 3);
-                cellv[r][v] = kidx[cell] < 0 ? base + ncx + 1 : cell;
-            }
-        }
-        return;
-    }
     bool near[ROWS][VEC];
 #pragma unroll
     for (int r = 0; r < ROWS; ++r)
-        find_eq1<VEC, 1>(cen4, ceny, ncx, rowbase[r], g.wgt, x, yb + r, pl + r, pa + r, pb + r,
-                         near + r, cellv + r);
+        find_row<VEC, DIST>(cen4, ceny, ncx, rowbase[r], g.wgt, x, yb + r, pl[r], pa[r], pb[r],
+                            near[r], cellv[r]);
     // near ties (a few pixels per frame): the reference argmin, after the
     // fast pass, whose keys are then dead, and inline (a call would pin the
     // fast pass's live values to the callee-saved registers)
@@ -300,10 +288,15 @@ __device__ __forceinline__ void find_cells(const float4* cen4, const float* ceny
 #pragma unroll
             for (int v = 0; v < VEC; ++v) {
                 if (!near[r][v]) continue;
-                const int slot = reference_slot(cen4, ceny, rowbase[r], ncx, pl[r][v], pa[r][v],
-                                                pb[r][v], static_cast<float>(x + v),
-                                                static_cast<float>(yb + r), g.wgt);
+                const float xf = static_cast<float>(x + v), yf = static_cast<float>(yb + r);
+                const int slot = DIST == 1 ? squared_slot(cen4, ceny, rowbase[r], ncx, pl[r][v], pa[r][v],
+                                                          pb[r][v], xf, yf, g.wgt)
+                                           : reference_slot(cen4, ceny, rowbase[r], ncx, pl[r][v],
+                                                            pa[r][v], pb[r][v], xf, yf, g.wgt);
                 cellv[r][v] = rowbase[r] + (slot / 3) * ncx + (slot % 3);
+                // (squared: a cell outside the grid comes first only where no
+                // distance is finite; the own cell is then taken)
+                if (DIST == 1 && kidx[cellv[r][v]] < 0) cellv[r][v] = rowbase[r] + ncx + 1;
             }
         }
     }
