@@ -41,7 +41,7 @@ HBM_PEAK_GBPS = 8000.0
 # instructions per second, x 2 for a fused multiply-add = 78.6 T ops/s
 VALU_ISSUE_PEAK_T = 39.32
 ALU_PEAK_TFLOPS = 78.64
-# algorithmic FP32 operations per pixel of one association launch: Eq. 1 for
+# algorithmic FP32 operations per pixel of one association round: Eq. 1 for
 # each of 9 candidates (3 colour and 2 position differences, 5 squares, 3
 # additions, 2 square roots, the product with m/S and the final sum: 17),
 # 8 comparisons for the argmin, and 5 additions into the centre sums
@@ -49,14 +49,17 @@ ASSIGN_OPS_PER_PIXEL = 9 * 17 + 8 + 5
 VALU_FILE = os.path.join(ROOT, "profiles", "assign_valu_counters.json")
 METRIC = "frames/s & Mpix/s/iter at 640x480 and 1080p; learned vs plain at equal energy"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "assign_c2_traffic.json")
-ASSIGN_SRC = os.path.join(ROOT, "paper_1509_04232_amd", "csrc", "assign.hip")
+ASSIGN_SRCS = [os.path.join(ROOT, "paper_1509_04232_amd", "csrc", f)
+               for f in ("assign.hip", "assign_tile.h", "rounds.hip")]
 
 
 def assign_bytes(n_pixels: int, n_clusters: int) -> int:
-    """Algorithmic bytes of one association launch that another association
-    follows (every launch these timings measure): read Lab (12 B/pixel),
-    read each centre (20 B) and add its five sums and count (48 B).  The
-    labels (4 B/pixel more) are written by the last launch of a frame only."""
+    """Algorithmic bytes of one association that another association follows
+    (every round these timings measure): read Lab (12 B/pixel), read each
+    centre (20 B) and add its five sums and count (48 B).  The labels
+    (4 B/pixel more) are written by the last association of a frame only.
+    (Where a frame's rounds are one launch, its pixels stay in registers: a
+    round then reads no Lab from memory.)"""
     return 12 * n_pixels + 68 * n_clusters
 
 
@@ -126,10 +129,11 @@ def event_frames_ms(torch, frame: Frame, steps: int, iters: int, enforce: bool) 
 
 
 def assign_from_frames_ms(torch, frame: Frame, steps: int, reps: int = 5) -> float:
-    """Average duration (ms) of one association launch inside frames: each
-    round of a frame is one association launch, so (frame with 10 rounds -
-    frame with 0 rounds) / 10, both timed with HIP events on the launch
-    stream (no connectivity); median of `reps` repetitions."""
+    """Average duration (ms) of one association round inside frames: (frame
+    with 10 rounds - frame with 0 rounds) / 10, both timed with HIP events on
+    the launch stream (no connectivity); median of `reps` repetitions.  The
+    rounds of a frame are one launch where its tiles fit the chip at once,
+    else one launch each."""
     runs = []
     for _ in range(reps):
         t10 = event_frames_ms(torch, frame, steps, 10, False)
@@ -157,7 +161,7 @@ def time_frames_with_upload(torch, frame: Frame, steps: int, warmup: int) -> flo
     return (time.perf_counter() - t0) / steps
 
 
-KERNELS = ("lab_seed", "assign", "ccl_", "energy")
+KERNELS = ("lab_seed", "assign_rounds", "assign", "ccl_", "energy")
 
 
 def kernel_times(slic, torch, frame: Frame, steps: int, iters: int, enforce: bool):
@@ -621,14 +625,22 @@ def bench_cleanup(slic, torch, dev, reps: int):
     return res
 
 
+def assign_src_sha256() -> str:
+    """One hash over the sources of the association kernels."""
+    h = hashlib.sha256()
+    for path in ASSIGN_SRCS:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
+
+
 def traffic_from_profile():
-    """HBM bytes per association launch from the committed PMC summary, or
+    """HBM bytes per association round from the committed PMC summary, or
     None if it is missing or the kernel source changed since."""
     try:
         with open(TRAFFIC_FILE) as f:
             t = json.load(f)
-        src = hashlib.sha256(open(ASSIGN_SRC, "rb").read()).hexdigest()
-        if t.get("assign_src_sha256") != src:
+        if t.get("assign_src_sha256") != assign_src_sha256():
             return None
         return t.get("bytes_per_launch")
     except (OSError, ValueError):
@@ -687,8 +699,7 @@ def valu_from_profile():
     try:
         with open(VALU_FILE) as f:
             v = json.load(f)
-        src = hashlib.sha256(open(ASSIGN_SRC, "rb").read()).hexdigest()
-        if v.get("assign_src_sha256") != src:
+        if v.get("assign_src_sha256") != assign_src_sha256():
             return None
         return v
     except (OSError, ValueError):
@@ -795,9 +806,7 @@ def main() -> int:
     roofline = {"bound": "alu", "achieved": round(tflops, 3), "peak": ALU_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(tflops / ALU_PEAK_TFLOPS, 4),
                 "traffic": traffic_from_profile(),
-                "kernel": f"assign_kernel (variant {frame.variant}: "
-                          f"{'x'.join(map(str, slic.slic_assign_variant_info(frame.variant)[:2]))} "
-                          f"pixels per thread)",
+                "kernel": "rounds_kernel (one of the frame's ten rounds)",
                 "avg_launch_us": round(a_ms * 1e3, 3),
                 "ops_per_pixel": ASSIGN_OPS_PER_PIXEL, "ops_per_launch": ops,
                 "hbm": {"bytes_per_launch": nbytes, "achieved_gbps": round(gbps, 1),
