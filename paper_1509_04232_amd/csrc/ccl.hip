@@ -562,6 +562,157 @@ __global__ __launch_bounds__(kBlock) void ccl_relabel_kernel(CclImage single, Cc
     }
 }
 
+// All four passes of a small frame in one workgroup, its links and sizes in
+// LDS: the unions across tile borders, the flattening, the joins with the
+// numbering, and the relabelling, with a barrier for a launch between them.
+// Bound by those chains of LDS round trips and, in a one-call segmentation
+// of a thumbnail, by the host's launches (2.5 us each), of which it saves
+// three.  One workgroup has one compute unit's LDS pipe, so its time grows
+// with the frame.  A whole frame, in us, with it and with the four launches:
+// 48 x 40 29.1 and 35.3; 96 x 72 34.0 and 40.2, on noise 35.4 and 48.1;
+// 128 x 128 (which would also need more than 64 KB of LDS) 49.2 and 45.9, on
+// noise 52.2 and 53.8.
+constexpr int kSmallThreads = 1024, kSmallPx = 8;
+constexpr int kSmallMax = 8000;  // 64 KB of LDS with the counts
+
+__device__ __forceinline__ int lds_load(const int* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void lds_store(int* p, int v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ int lds_root(const int* P, int i) {
+    for (int p = lds_load(P + i); p != i; p = lds_load(P + i)) i = p;
+    return i;
+}
+
+__global__ __launch_bounds__(kSmallThreads) void ccl_small_kernel(CclImage g, Divisor by_w,
+                                                                  Divisor by_h) {
+    extern __shared__ int s_small[];  // n links, then n sizes (later ranks and joins)
+    __shared__ int part[kSmallPx * (kSmallThreads / 64)];
+    __shared__ int wave_part[kSmallPx * (kSmallThreads / 64) / 64];
+    const int w = g.w, h = g.h, n = w * h;
+    int* const P = s_small;
+    int* const C = s_small + n;
+    gmem<const int32_t>* labels = as_global(g.labels);  // may be the output
+    gmem<const int>* __restrict__ lroot = as_global(g.lroot);
+    gmem<const int>* __restrict__ size = as_global(g.size);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // links to the tile-local roots; their sizes (0: not a local root)
+    int lr[kSmallPx], sz[kSmallPx];
+#pragma unroll
+    for (int j = 0; j < kSmallPx; ++j) {
+        const int i = min(static_cast<int>(threadIdx.x) + j * kSmallThreads, n - 1);
+        lr[j] = lroot[i];
+        sz[j] = size[i];  // (read where only a local root's is set, used for those alone)
+    }
+#pragma unroll
+    for (int j = 0; j < kSmallPx; ++j) {
+        const int i = threadIdx.x + j * kSmallThreads;
+        if (i >= n) continue;
+        const int y = by_w.quotient(i), x = i - y * w;
+        const int r = ((y & ~(kTile - 1)) + lr[j] / kTile) * w + (x & ~(kTile - 1)) + lr[j] % kTile;
+        P[i] = r;
+        C[i] = r == i ? sz[j] : 0;
+    }
+    __syncthreads();
+    // unions across the tiles' left and top borders, as in the border pass
+    const int upright = ((w - 1) / kTile) * h, level = ((h - 1) / kTile) * w;
+    for (int q = threadIdx.x; q < upright + level; q += kSmallThreads) {
+        int i, o, along, t;
+        if (q < upright) {
+            const int b = by_h.quotient(q), y = q - b * h;
+            i = y * w + (b + 1) * kTile;
+            o = i - 1;
+            along = w;
+            t = y;
+        } else {
+            const int b = by_w.quotient(q - upright), x = q - upright - b * w;
+            i = (b + 1) * kTile * w + x;
+            o = i - w;
+            along = 1;
+            t = x;
+        }
+        const bool first = (t & (kTile - 1)) == 0;
+        const int back = first ? 0 : along;
+        const int mine = labels[i], other = labels[o];
+        const int before = labels[i - back], other_before = labels[o - back];
+        if (mine != other || (!first && before == mine && other_before == mine)) continue;
+        int a = i, c = o;
+        for (;;) {
+            a = lds_root(P, a);
+            c = lds_root(P, c);
+            if (a == c) break;
+            const int hi = max(a, c), lo = min(a, c);
+            const int old = atomicMin(P + hi, lo);
+            if (old == hi) break;
+            a = old;
+            c = lo;
+        }
+    }
+    __syncthreads();
+    // component roots; a local root that is none adds its part's size
+    for (int i = threadIdx.x; i < n; i += kSmallThreads) {
+        const int r = lds_root(P, i);
+        lds_store(P + i, r);
+        if (r != i && C[i] > 0) atomicAdd(C + r, C[i]);
+    }
+    __syncthreads();
+    // the survivors' ranks in raster order, the others' joins
+    int rank[kSmallPx];
+    bool survives[kSmallPx];
+#pragma unroll
+    for (int j = 0; j < kSmallPx; ++j) {
+        const int i = threadIdx.x + j * kSmallThreads;
+        const bool root = i < n && P[min(i, n - 1)] == i;
+        survives[j] = root && (i == 0 || !is_small(g, C[i]));
+        const unsigned long long b = __ballot(survives[j]);
+        if (lane == 0) part[j * (kSmallThreads / 64) + wave] = __popcll(b);
+        rank[j] = __popcll(b & ((1ull << lane) - 1ull));
+        if (root && !survives[j]) C[i] = -2 - P[i - by_w.quotient(i) * w > 0 ? i - 1 : i - w];
+    }
+    __syncthreads();
+    constexpr int kParts = kSmallPx * (kSmallThreads / 64);  // a thread each
+    static_assert(kParts == 128 && kSmallMax <= kSmallThreads * kSmallPx,
+                  "two wavefronts scan the counts");
+    int own = 0, inc = 0;
+    if (threadIdx.x < kParts) {
+        own = inc = part[threadIdx.x];
+        for (int d = 1; d < 64; d <<= 1) {
+            const int v = __shfl_up(inc, d);
+            if (lane >= d) inc += v;
+        }
+        if (lane == 63) wave_part[wave] = inc;
+    }
+    __syncthreads();
+    if (threadIdx.x < kParts) {
+        int base = 0;
+        for (int q = 0; q < wave; ++q) base += wave_part[q];
+        part[threadIdx.x] = base + inc - own;
+        if (threadIdx.x == kParts - 1 && g.n_segments) *as_global(g.n_segments) = base + inc;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kSmallPx; ++j)
+        if (survives[j])
+            C[threadIdx.x + j * kSmallThreads] = part[j * (kSmallThreads / 64) + wave] + rank[j];
+    __syncthreads();
+    // final labels: the joins followed to a survivor; each step gives the root
+    // before it the value (a rank, or a later join) that it read, so that the
+    // walks through the same chain find it shorter
+    gmem<int32_t>* out = as_global(g.out);
+    for (int i = threadIdx.x; i < n; i += kSmallThreads) {
+        int at = P[i], k = lds_load(C + at);
+        while (k < 0) {
+            const int next = -2 - k;
+            k = lds_load(C + next);
+            lds_store(C + at, k);
+            at = next;
+        }
+        out[i] = k;
+    }
+}
+
 }  // namespace
 
 int scan_tiles_for(int n) { return (n + kMergeBlock - 1) / kMergeBlock; }
@@ -609,6 +760,11 @@ hipError_t launch_connectivity(const Workspace& ws, int32_t w, int32_t h, const 
     const dim3 grid((w + kTile - 1) / kTile, (h + kTile - 1) / kTile);
     if (!local_done)
         SLIC_STEP("ccl_local", ccl_local_kernel<false><<<grid, kBlock, 0, s>>>(c, none));
+    if (w * h <= kSmallMax) {  // the times on both sides stand at the kernel
+        SLIC_STEP("ccl_small", ccl_small_kernel<<<1, kSmallThreads, 2 * sizeof(int) * w * h, s>>>(
+                                   c, make_divisor(w), make_divisor(h)));
+        return hipSuccess;
+    }
     SLIC_STEP("ccl_border", ccl_border_kernel<false><<<grid, 2 * kTile, 0, s>>>(c, none));
     SLIC_STEP("ccl_flatten", ccl_flatten_kernel<false><<<grid, kBlock, 0, s>>>(c, none));
     SLIC_STEP("ccl_merge",
