@@ -26,7 +26,11 @@
 // Convergence stop: each tile also stores the shift of the centres it owns, as
 // it stages them, in a word that carries the round; before the next round
 // every workgroup adds up all tiles' words (stored half a round before) and
-// takes the same decision.
+// takes the same decision.  Centres that come from the image move by less than
+// 3 S <= 255 pixels or 256 units of colour, so the shifts of a window's at most
+// 64 cells stay below 64 x 5 x 2^26 < 2^35.  A given centre may lie anywhere: a
+// shift from 2^39 on goes whole into a second word, stored before the first,
+// which then says so; the sums are those of 64-bit words in any case.
 //
 // Why every wait ends.  The launch does not assume that all its workgroups
 // run at once.  Each workgroup registers (a bit in a census word) before its
@@ -64,6 +68,14 @@ constexpr int kMaxRounds = (1 << 14) - 1;
 constexpr int kPosBits = 19;
 constexpr unsigned kPosMask = (1u << kPosBits) - 1;
 constexpr long long kBias = 1ll << 40;
+// A shift word: the round as above; below it a shift under kWideShift, or
+// kWideMark: the shift is the tile's word in `wide`.  The narrow shifts of all
+// tiles add up to less than kWideMark.
+constexpr unsigned long long kPayload = (1ull << (32 + kTagShift)) - 1;
+constexpr unsigned long long kWideShift = 1ull << 39, kWideMark = 1ull << 49;
+static_assert(kMaxTiles * kWideShift <= kWideMark && kMaxTiles * kWideMark > kWideMark &&
+                  kWideMark <= kPayload && 64ull * 5 * (1ull << 26) < kWideShift,
+              "no sum of shifts reaches the round or the mark");
 
 struct RoundsArgs {
     AssignImage g;
@@ -80,6 +92,7 @@ struct RoundsArgs {
     int census_ticks;
     long long limit;     // convergence stop: after a round whose shift is below it
     unsigned long long* shift;  // two buffers of n_tiles words, zero before the launch
+    unsigned long long* wide;   // the same, not cleared: read only where a shift word says so
     int32_t* rounds_run;        // with converge (may be null)
 };
 
@@ -257,23 +270,37 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
         if constexpr (kConv) {
             if (round > checked) {
                 // the shift of the round before, from all tiles
+                const size_t buffer = (round & 1) ? 0 : a.n_tiles;
                 gmem<const unsigned long long>* const in =
-                    as_global(static_cast<const unsigned long long*>(a.shift)) +
-                    ((round & 1) ? 0 : a.n_tiles);
-                unsigned long long mine = 0;
-                for (int j = threadIdx.x; j < a.n_tiles; j += kThreads) {
+                    as_global(static_cast<const unsigned long long*>(a.shift)) + buffer;
+                gmem<const unsigned long long>* const wide =
+                    as_global(static_cast<const unsigned long long*>(a.wide)) + buffer;
+                auto sum_of_tiles = [&](auto shift_of) {
+                    unsigned long long mine = 0;
+                    for (int j = threadIdx.x; j < a.n_tiles; j += kThreads) mine += shift_of(j);
+                    for (int d = 32; d > 0; d >>= 1) mine += __shfl_xor(mine, d);
+                    if ((threadIdx.x & 63) == 0) s_total[threadIdx.x >> 6] = mine;
+                    __syncthreads();
+                    unsigned long long total = 0;
+#pragma unroll
+                    for (int q = 0; q < kThreads / 64; ++q) total += s_total[q];
+                    return total;
+                };
+                unsigned long long total = sum_of_tiles([&](int j) {
                     unsigned long long v;
                     while ((v = agent_load<unsigned long long>(in + j)) >> (32 + kTagShift) !=
                            static_cast<unsigned>(round)) {
                     }
-                    mine += v & ((1ull << (32 + kTagShift)) - 1);
+                    return v & kPayload;
+                });
+                if (total >= kWideMark) {  // again, with the marked tiles' own words
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                    __syncthreads();  // s_total is read
+                    total = sum_of_tiles([&](int j) {
+                        const unsigned long long v = agent_load<unsigned long long>(in + j) & kPayload;
+                        return v == kWideMark ? agent_load<unsigned long long>(wide + j) : v;
+                    });
                 }
-                for (int d = 32; d > 0; d >>= 1) mine += __shfl_xor(mine, d);
-                if ((threadIdx.x & 63) == 0) s_total[threadIdx.x >> 6] = mine;
-                __syncthreads();
-                unsigned long long total = 0;
-#pragma unroll
-                for (int q = 0; q < kThreads / 64; ++q) total += s_total[q];
                 if (static_cast<long long>(total) < a.limit) break;
                 checked = round;
             }
@@ -376,9 +403,16 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
         __syncthreads();
         if constexpr (kConv) {
             if (threadIdx.x == 0) {  // (the next additions are two barriers away)
+                const size_t at = ((round & 1) ? a.n_tiles : 0) + T;
+                unsigned long long v = s_shift;
+                if (v >= kWideShift) {
+                    agent_store<unsigned long long>(as_global(a.wide) + at, v);
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                    v = kWideMark;
+                }
                 agent_store<unsigned long long>(
-                    as_global(a.shift) + ((round & 1) ? a.n_tiles : 0) + T,
-                    s_shift | (static_cast<unsigned long long>(round + 1) << (32 + kTagShift)));
+                    as_global(a.shift) + at,
+                    v | (static_cast<unsigned long long>(round + 1) << (32 + kTagShift)));
                 s_shift = 0;
             }
         }
@@ -577,7 +611,10 @@ bool rounds_args(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int v
     a->part_words = static_cast<size_t>(a->n_tiles) * a->cells * 4;
     // the connectivity buffers are free until the clean-up: census and partial
     // sums lie in the ranks and local roots (adjacent arrays)
+    // (and the shifts too wide for their words in the labels' parents)
     const size_t n = static_cast<size_t>(w) * h * sizeof(int32_t);
+    a->wide = reinterpret_cast<unsigned long long*>(ws.ccl0);
+    if (2 * static_cast<size_t>(a->n_tiles) * sizeof(unsigned long long) > n) return false;
     a->census = reinterpret_cast<unsigned long long*>(ws.ccl2);
     a->shift = a->census + kMaxWords * kCensusStride;
     a->part = a->shift + 2 * a->n_tiles;

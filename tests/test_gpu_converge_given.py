@@ -1,0 +1,71 @@
+"""The convergence stop on contexts made from given centres, which may lie
+anywhere: shifts far beyond the image's own range, against the oracle's
+composition (labels, centres and counts bit for bit, and the rounds run, from
+the exact sum of the shifts)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+MAX_ROUNDS = 6
+
+
+@pytest.fixture(scope="module")
+def slic():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    import paper_1509_04232_amd as slic
+    return slic
+
+
+def compose(lab, S, m, cen, dist, threshold):
+    """Rounds of (update, associate) until the rule of Section 2."""
+    labels = oracle.assign(lab, S, m, cen, dist)
+    limit = int(np.rint(threshold * 2.0 ** 18)) * len(cen)
+    for rounds in range(1, MAX_ROUNDS + 1):
+        prev = cen
+        cen, cnt = oracle.update(lab, labels, cen)
+        labels = oracle.assign(lab, S, m, cen, dist)
+        if oracle.residual(prev, cen) < limit:
+            break
+    return labels, cen, cnt, rounds
+
+
+@pytest.mark.parametrize("squared", [False, True])
+@pytest.mark.parametrize("w,h,S,m", [(96, 72, 8, 0.0), (160, 120, 16, 10.0), (333, 251, 27, 0.0),
+                                     (700, 500, 16, 10.0)])
+@pytest.mark.parametrize("far,every,threshold", [
+    # about 2^39 per centre: all centres, one in nine
+    (2.0 ** 21, 1, 1.0), (2.0 ** 21 - 1, 9, 1.0),
+    # 2^51 to 2^58 per centre
+    (2.0 ** 33, 1, 1.0), (1e10, 9, 1.0), (1e12, 99, 1.0),
+    # thresholds on either side of the first round's shift
+    (1e10, 1, 9e9), (1e10, 1, 2e10),
+])
+def test_far_given_centres_converge(slic, squared, w, h, S, m, far, every, threshold):
+    img = synth.voronoi_image(w + S, w, h, max(2, w * h // 900), 8.0)
+    dist = oracle.DIST_SQUARED if squared else oracle.DIST_EQ1
+    lab = oracle.rgb_to_lab(img)
+    cen = oracle.kmeans(lab, S, 10.0, True, 2)[1].copy()
+    cen[::every, 3] += np.float32(far)
+    assert len(cen[::every]) * 1.01 * far * 2.0 ** 18 < 2.0 ** 63
+    want = compose(lab, S, m, cen, dist, threshold)
+    p = slic.Params(w, h, S=S, m=m, squared_distance=squared)
+    ctx = slic.Context(p, torch.from_numpy(np.ascontiguousarray(img).reshape(-1)).cuda(),
+                       centres=torch.from_numpy(cen).cuda())
+    if threshold * 2.0 ** 18 * len(cen) > 4e18:  # beyond what the call accepts
+        with pytest.raises(slic.SlicError):
+            ctx.iterate_converge(MAX_ROUNDS, threshold)
+        return
+    n = ctx.iterate_converge(MAX_ROUNDS, threshold)
+    lb, (got, cnt) = ctx.labels(), ctx.centres()
+    torch.cuda.synchronize()
+    assert int(n.cpu()[0]) == want[3]
+    assert np.array_equal(lb.cpu().numpy(), want[0])
+    assert np.array_equal(got.cpu().numpy(), want[1])
+    assert np.array_equal(cnt.cpu().numpy(), want[2])
+    ctx.close()
