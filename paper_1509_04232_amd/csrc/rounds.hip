@@ -89,7 +89,6 @@ struct RoundsArgs {
     int n;            // rounds, >= 2
     int store_last;   // the last round stores the labels
     int sums_last;    // the last round adds its sums to the ring
-    int census_ticks;
     long long limit;     // convergence stop: after a round whose shift is below it
     unsigned long long* shift;  // two buffers of n_tiles words, zero before the launch
     unsigned long long* wide;   // the same, not cleared: read only where a shift word says so
@@ -126,7 +125,7 @@ __device__ __forceinline__ void take_census(const RoundsArgs& a, unsigned* words
                                : static_cast<unsigned>(v);
         }
         if (__all(ready)) break;
-        if (wall_clock64() - began < a.census_ticks) {
+        if (wall_clock64() - began < kCensusTicks) {
             __builtin_amdgcn_s_sleep(2);
             continue;
         }
@@ -251,7 +250,7 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
         const unsigned long long v = __hip_atomic_fetch_or(
             as_global(a.census) + (me / kCensusBits) * kCensusStride, 1ull << (me % kCensusBits),
             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_late = (v & kFrozen) != 0;
+        s_late = (v & kFrozen) && !((v >> (32 + me % kCensusBits)) & 1ull);
         s_shift = 0;
     }
     load_centre();
@@ -531,6 +530,15 @@ __global__ __launch_bounds__(256) void clear_words_kernel(uint4* p, size_t n) {
     if (i < n) p[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
+// A census frozen from the start, without the workgroups that `absent` names.
+__global__ __launch_bounds__(64) void freeze_census_kernel(unsigned long long* census, int n_tiles,
+                                                           uint32_t absent) {
+    const int in_word = min(n_tiles - static_cast<int>(threadIdx.x) * kCensusBits, kCensusBits);
+    if (in_word <= 0) return;
+    const unsigned here = ((1u << in_word) - 1u) & ~absent;
+    census[threadIdx.x * kCensusStride] = kFrozen | (static_cast<unsigned long long>(here) << 32);
+}
+
 template <int VEC, int ROWS, int DIST, int SRC, bool kConv>
 hipError_t launch_rounds_as(const RoundsArgs& a, hipStream_t s) {
     KernelTimer timer("assign_rounds", s);
@@ -654,23 +662,28 @@ uint32_t* rounds_clear(const Workspace& ws, int32_t w, int32_t h, const Grid& g,
 
 hipError_t launch_rounds(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int64_t t0, int n,
                          int variant, bool store_last, bool sums_last, bool cleared, hipStream_t s,
-                         const RoundsStop* stop, int census_ticks) {
+                         const RoundsStop* stop, const RoundsTest* test) {
     RoundsArgs a;
     int sources = 0;
-    if (n < 2 || n > kMaxRounds || !rounds_args(ws, w, h, g, variant, compute_units(), &a, &sources))
+    const int cus = compute_units();
+    if (n < 2 || n > kMaxRounds || !rounds_args(ws, w, h, g, variant, cus, &a, &sources))
+        return hipErrorInvalidValue;
+    // workgroups said to take part must be able to run together
+    if (test && (a.n_tiles > cus ||
+                 !(((1u << std::min(a.n_tiles, kCensusBits)) - 1u) & ~test->absent)))
         return hipErrorInvalidValue;
     a.g = assign_image(ws, w, h, g, variant);
     a.t0 = t0;
     a.n = n;
     a.store_last = store_last;
     a.sums_last = sums_last;
-    a.census_ticks = census_ticks < 0 ? static_cast<int>(kCensusTicks) : census_ticks;
     if (!cleared) {
         const size_t words = clear_words(a);
         KernelTimer timer("assign_clear", s);
         clear_words_kernel<<<static_cast<unsigned>((words + 1023) / 1024), 256, 0, s>>>(
             reinterpret_cast<uint4*>(a.census), words / 4);
     }
+    if (test) freeze_census_kernel<<<1, 64, 0, s>>>(a.census, a.n_tiles, test->absent);
     a.limit = stop ? stop->limit : 0;
     a.rounds_run = stop ? stop->rounds_run : nullptr;
     return rounds_fn(variant, g.dist, sources, stop != nullptr)(a, s);

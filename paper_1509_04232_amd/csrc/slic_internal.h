@@ -164,21 +164,25 @@ hipError_t launch_assign_final_ccl(const Workspace& ws, int32_t w, int32_t h, co
 // does not suit.  The words that
 // rounds_clear names must be zero: `cleared` says that an earlier launch of
 // the stream has done so, else the call does.
-// census_ticks: how long a workgroup waits for the others to start, in
-// 10 ns (negative: the built-in time).
 // stop: end after a round whose quantised shift of all centres is below limit,
 // and write the rounds run (device int32, may be null).
+// test: a launch some of whose workgroups come too late to take part, as on a
+// shared chip: the workgroups b with bit b % 31 of `absent` (not for a frame
+// with more tiles than compute units, nor without any that takes part).
 constexpr int kMinRounds = 2;
 struct RoundsStop {
     long long limit;
     int32_t* rounds_run;
+};
+struct RoundsTest {
+    uint32_t absent;
 };
 int rounds_variant(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int variant, int n);
 uint32_t* rounds_clear(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int variant,
                        size_t* words);
 hipError_t launch_rounds(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int64_t t0, int n,
                          int variant, bool store_last, bool sums_last, bool cleared, hipStream_t s,
-                         const RoundsStop* stop = nullptr, int census_ticks = -1);
+                         const RoundsStop* stop = nullptr, const RoundsTest* test = nullptr);
 hipError_t launch_assign_batch(const AssignTileMap& map, int total_tiles, int min_S, int64_t t,
                                int variant, int dist, hipStream_t s, bool store_labels = true);
 AssignImage assign_image(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int variant);
@@ -288,3 +292,10 @@ struct slic_ctx {
     int state;      // 0: k-means state valid, 1: connectivity done, 2: poisoned,
                     // 3: stopped by the convergence rule (final)
 };
+
+// For the tests, no part of the ABI: slic_iterate(ctx, n), or with threshold
+// >= 0 slic_iterate_converge(ctx, n, threshold, d_iters_done), as one rounds
+// launch without the workgroups that RoundsTest::absent names; SLIC_EINVAL
+// where the frame has no such launch.
+extern "C" int slic_test_rounds(slic_ctx* ctx, int32_t n, uint32_t absent, float threshold,
+                                int32_t* d_iters_done);

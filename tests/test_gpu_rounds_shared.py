@@ -1,0 +1,95 @@
+"""The rounds launch (csrc/rounds.hip) when some of its workgroups start too
+late to take part, as on a chip that other streams share, bit for bit against
+the oracle.  slic_test_rounds (csrc/slic_internal.h) names those workgroups, so
+that every run takes this path; bit b of `absent` stands for the workgroups
+b, b + 31, b + 62, ..."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+ABSENT = [0x1, 0x55555555, 0x7FFFFFFD, 0x7FFFFBFE, 0x0]
+
+
+@pytest.fixture(scope="module")
+def slic():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    import paper_1509_04232_amd as slic
+    return slic
+
+
+def _rounds(slic, ctx, n, absent, threshold=-1.0):
+    fn = slic._abi.lib.slic_test_rounds
+    fn.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_uint32, ctypes.c_float, ctypes.c_void_p]
+    done = torch.full((1,), -1, dtype=torch.int32, device="cuda")
+    assert fn(ctx.ctx, n, absent, threshold, done.data_ptr()) == slic.SLIC_OK
+    return done
+
+
+def _gpu(img):
+    return torch.from_numpy(np.ascontiguousarray(img).reshape(-1)).cuda()
+
+
+@pytest.fixture
+def variant(slic):
+    held = []
+
+    def choose(w, h, S, v):
+        slic.slic_set_assign_variant(w, h, S, v)
+        held.append((w, h, S))
+    yield choose
+    for key in held:
+        slic.slic_set_assign_variant(*key, 0)
+
+
+SHAPES = [(64, 48, 8, 0), (97, 75, 8, 0), (300, 200, 16, 0), (333, 51, 27, 3), (640, 480, 16, 5),
+          (480, 320, 10, 7)]
+
+
+@pytest.mark.parametrize("squared", [False, True])
+@pytest.mark.parametrize("absent", ABSENT)
+@pytest.mark.parametrize("w,h,S,v", SHAPES)
+def test_rounds_without_all_workgroups(slic, variant, w, h, S, v, absent, squared):
+    img = synth.voronoi_image(w + h + S, w, h, max(2, w * h // 900), 8.0)
+    dist = oracle.DIST_SQUARED if squared else oracle.DIST_EQ1
+    variant(w, h, S, v)
+    ctx = slic.Context(slic.Params(w, h, S=S, m=10.0, squared_distance=squared), _gpu(img))
+    done = 0
+    for n, shared in ((2, True), (3, True), (1, False), (2, False), (4, True)):
+        if shared:
+            _rounds(slic, ctx, n, absent)
+        else:
+            ctx.iterate(n)
+        done += n
+        want = oracle.segment(img, S, 10.0, done, True, False, 0, oracle.COLOR_LAB, dist)
+        lb, (cen, cnt) = ctx.labels(), ctx.centres()
+        torch.cuda.synchronize()
+        assert np.array_equal(lb.cpu().numpy(), want["labels"]), done
+        assert np.array_equal(cen.cpu().numpy(), want["centres"]), done
+        assert np.array_equal(cnt.cpu().numpy(), want["counts"]), done
+    ctx.close()
+
+
+@pytest.mark.parametrize("threshold", [0.0, 0.3, 1.0, 1e4])
+@pytest.mark.parametrize("absent", ABSENT)
+@pytest.mark.parametrize("w,h,S,v", SHAPES[:3] + SHAPES[4:5])
+def test_convergence_stop_without_all_workgroups(slic, variant, w, h, S, v, absent, threshold):
+    img = synth.voronoi_image(3 * w + S, w, h, max(2, w * h // 900), 8.0)
+    want = oracle.kmeans_converge(oracle.rgb_to_lab(img), S, 10.0, True, 12, threshold)
+    variant(w, h, S, v)
+    ctx = slic.Context(slic.Params(w, h, S=S, m=10.0), _gpu(img))
+    n = _rounds(slic, ctx, 12, absent, threshold)
+    lb, (cen, cnt) = ctx.labels(), ctx.centres()
+    torch.cuda.synchronize()
+    assert int(n.cpu()[0]) == want[3]
+    assert np.array_equal(lb.cpu().numpy(), want[0])
+    assert np.array_equal(cen.cpu().numpy(), want[1])
+    assert np.array_equal(cnt.cpu().numpy(), want[2])
+    ctx.close()
