@@ -317,7 +317,6 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
 
         // ---- the window's centres
         if (i < ncells) {
-            if (!all_here) load_centre();
             long long s0 = 0, s1 = 0, n = 0;
             if (round > 0 && k >= 0) {  // (no words to wait for where there is no centre)
                 gmem<const char>* const in = reinterpret_cast<gmem<const char>*>(
@@ -356,6 +355,15 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
                 s0 = sp[comp];
                 s1 = sp[4];
                 n = sp[5];
+            }
+            // With a frozen census the centre of the round before may come from
+            // another workgroup.  Its owner stored it before the word of that
+            // round seen above, so only a load after the wait is sure to find
+            // it.  (A centre stored in this round has pixels: v0, v1 are not
+            // used then.)
+            if (!all_here) {
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                load_centre();
             }
             const double dn = static_cast<double>(n > 0 ? n : 1);
             const double inv = 1.0 / static_cast<double>(1 << kQShift);

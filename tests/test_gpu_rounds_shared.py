@@ -93,3 +93,37 @@ def test_convergence_stop_without_all_workgroups(slic, variant, w, h, S, v, abse
     assert np.array_equal(cen.cpu().numpy(), want[1])
     assert np.array_equal(cnt.cpu().numpy(), want[2])
     ctx.close()
+
+
+@pytest.mark.parametrize("w,h,S,v,m", [(97, 75, 8, 0, 0.0), (300, 200, 16, 0, 0.0),
+                                       (640, 480, 16, 5, 0.0), (480, 320, 10, 7, 0.1)])
+def test_clusters_that_empty_after_they_moved(slic, variant, w, h, S, v, m):
+    """Noise of three colours: clusters lose their last pixel in the round
+    after their centre moved, and keep the centre of that round.  With one
+    workgroup in 31 absent, some have two tiles and are half a round behind
+    their neighbours."""
+    rng = np.random.default_rng(w)
+    pal = rng.integers(0, 256, (3, 3), dtype=np.uint8)
+    img = pal[rng.integers(0, 3, (h, w))]
+    lab = oracle.rgb_to_lab(img)
+    cen = oracle.kmeans(lab, S, m, True, 0)[1]
+    labels = oracle.assign(lab, S, m, cen)
+    moved = np.zeros(len(cen), bool)
+    emptied = 0
+    for _ in range(6):
+        prev = cen
+        cen, cnt = oracle.update(lab, labels, prev)
+        emptied += int((moved & (cnt == 0)).sum())
+        moved = (cen != prev).any(1)
+        labels = oracle.assign(lab, S, m, cen)
+    assert emptied > 0
+    variant(w, h, S, v)
+    for absent in [1 << b for b in range(31)] + ABSENT:
+        ctx = slic.Context(slic.Params(w, h, S=S, m=m), _gpu(img))
+        _rounds(slic, ctx, 6, absent)
+        lb, (got, n) = ctx.labels(), ctx.centres()
+        torch.cuda.synchronize()
+        assert np.array_equal(lb.cpu().numpy(), labels)
+        assert np.array_equal(got.cpu().numpy(), cen)
+        assert np.array_equal(n.cpu().numpy(), cnt)
+        ctx.close()
