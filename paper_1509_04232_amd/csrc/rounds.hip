@@ -37,11 +37,14 @@
 // first store.  After its first tile it looks until every workgroup has
 // registered or 20 us have passed; then it freezes the words that are not
 // full, with the bits registered by then, in one atomic operation per word.
-// A workgroup that registers in a frozen word leaves at once.  So all
-// workgroups agree on who takes part, every one of them is running, and the
-// tiles of the others are divided among them.  Of all (round, tile) pairs not
-// yet done, one of the lowest round waits for nothing, and the workgroup that
-// has it is running and is held up only by pairs of rounds no later.
+// So all workgroups agree on who was there in time.  If all were, each keeps
+// its tile.  Else those in the census have done the first round of their own
+// tiles, and every workgroup, also one that starts later, takes the other
+// (round, tile) pairs from a common counter, the lower rounds first.  The lowest
+// pair not yet done is then always a running workgroup's, and waits only for
+// words of a round before, all done.  (With the convergence stop, a workgroup
+// ends at the first pair it takes beyond the last round; a round has as many
+// pairs as there are workgroups, so none takes one of the round after.)
 #include "assign_tile.h"
 
 #include <algorithm>
@@ -53,6 +56,7 @@ namespace {
 
 constexpr int kCensusBits = 31;    // workgroups per census word
 constexpr int kCensusStride = 16;  // words (128 bytes) between census words
+constexpr int kTicket = 8;         // word of the ticket counter, between two of them
 constexpr int kMaxTiles = 1024;
 constexpr int kMaxWords = (kMaxTiles + kCensusBits - 1) / kCensusBits;
 constexpr long long kCensusTicks = 2000;  // of the 100 MHz clock: 20 us
@@ -76,6 +80,9 @@ constexpr unsigned long long kWideShift = 1ull << 39, kWideMark = 1ull << 49;
 static_assert(kMaxTiles * kWideShift <= kWideMark && kMaxTiles * kWideMark > kWideMark &&
                   kWideMark <= kPayload && 64ull * 5 * (1ull << 26) < kWideShift,
               "no sum of shifts reaches the round or the mark");
+
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 
 struct RoundsArgs {
     AssignImage g;
@@ -104,10 +111,27 @@ __device__ __forceinline__ void agent_store(gmem<T>* p, T v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// n adjacent 32-bit words at p + i, of an array of `size`, in one store that the
+// XCDs' caches keep coherent (word by word, the labels of one round of a
+// 1024 x 1024 frame took 2 us more).
+template <int n, class F>
+__device__ __forceinline__ void store_through(int32_t* p, size_t size, size_t i, F word) {
+    constexpr int kRaw = 0x27000, kAgent = 16;  // 32-bit elements; the sc1 bit
+    const auto to = __builtin_amdgcn_make_buffer_rsrc(p, 0, static_cast<int>(size * 4), kRaw);
+    const int at = static_cast<int>(i * 4);
+    if constexpr (n == 4) {
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4{word(0), word(1), word(2), word(3)}, to, at, 0, kAgent);
+    } else if constexpr (n == 2) {
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2{word(0), word(1)}, to, at, 0, kAgent);
+    } else {
+        __builtin_amdgcn_raw_buffer_store_b32(word(0), to, at, 0, kAgent);
+    }
+}
+
 // Who takes part: waits for every workgroup to register, or freezes the
 // census.  Leaves the participants' bits in `words` (all of them to see after
 // the caller's barrier).
-__device__ __forceinline__ void take_census(const RoundsArgs& a, unsigned* words) {
+__device__ __forceinline__ void take_census(const RoundsArgs& a, long long ticks, unsigned* words) {
     const int lane = threadIdx.x;  // wave 0
     const int nwords = (a.n_tiles + kCensusBits - 1) / kCensusBits;
     gmem<unsigned long long>* const w = as_global(a.census) + lane * kCensusStride;
@@ -125,7 +149,7 @@ __device__ __forceinline__ void take_census(const RoundsArgs& a, unsigned* words
                                : static_cast<unsigned>(v);
         }
         if (__all(ready)) break;
-        if (wall_clock64() - began < kCensusTicks) {
+        if (wall_clock64() - began < ticks) {
             __builtin_amdgcn_s_sleep(2);
             continue;
         }
@@ -149,7 +173,7 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
     constexpr int kLogW = __builtin_ctz(Sh::kTileW), kLogH = __builtin_ctz(Sh::kTileH);
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ unsigned s_words[64];
-    __shared__ int s_late;
+    __shared__ int s_late, s_ticket;
     __shared__ unsigned long long s_shift, s_total[kThreads / 64];
     const AssignImage& g = a.g;
     const int S = g.S;
@@ -255,17 +279,19 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
     }
     load_centre();
     __syncthreads();
-    if (s_late) return;
+    const bool late = __builtin_amdgcn_readfirstlane(s_late) != 0;
     const unsigned long long mask =  // the summed fields of this thread's words
         comp < 3 ? (1ull << (32 + kTagShift)) - 1
                  : (1ull << (32 + kTagShift)) - 1 - (static_cast<unsigned long long>(kPosMask) << kPosBits);
 
     bool all_here = true;  // false: the census was frozen
-    int n_here = 0, my_place = 0;
+    int absent = 0;        // workgroups not in it
+    int taken = 0;         // pairs from the counter
     int T = me;
     int round = 0;  // association a.t0 + round
     int checked = 0;  // rounds whose shift has been looked at
-    for (bool first = true;; first = false) {
+    // One round of the tile at hand; false: the rounds before were the last.
+    auto pass = [&]() {
         if constexpr (kConv) {
             if (round > checked) {
                 // the shift of the round before, from all tiles
@@ -300,7 +326,10 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
                         return v == kWideMark ? agent_load<unsigned long long>(wide + j) : v;
                     });
                 }
-                if (static_cast<long long>(total) < a.limit) break;
+                if (static_cast<long long>(total) < a.limit) {
+                    if (T == 0 && threadIdx.x == 0 && a.rounds_run) *a.rounds_run = round;
+                    return false;
+                }
                 checked = round;
             }
         }
@@ -324,9 +353,14 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
                 unsigned long long w[SRC];
                 for (;;) {
 #pragma unroll
-                    for (int m = 0; m < SRC; ++m)
+                    for (int m = 0; m < SRC; ++m) {
+                        // (opaque: the sums base + offset would be kept in
+                        // two registers each through the loop)
+                        unsigned place = src[m];
+                        asm volatile("" : "+v"(place));
                         w[m] = agent_load<unsigned long long>(
-                            reinterpret_cast<gmem<const unsigned long long>*>(in + src[m]));
+                            reinterpret_cast<gmem<const unsigned long long>*>(in + place));
+                    }
                     unsigned off = 0;  // any bit: a word of another round
 #pragma unroll
                     for (int m = 0; m < SRC; ++m)
@@ -362,7 +396,7 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
             // it.  (A centre stored in this round has pixels: v0, v1 are not
             // used then.)
             if (!all_here) {
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");  // (keeps the order)
                 load_centre();
             }
             const double dn = static_cast<double>(n > 0 ? n : 1);
@@ -394,7 +428,8 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
                     agent_store<float>(c + comp, v0);
                     if (comp == 3) agent_store<float>(c + 4, v1);
                 }
-                if ((kConv || last) && t > 0 && comp == 3) as_global(g.counts)[k] = static_cast<int32_t>(n);
+                if ((kConv || last) && t > 0 && comp == 3)
+                    agent_store<int32_t>(as_global(g.counts) + k, static_cast<int32_t>(n));
                 if (a.sums_last && round >= a.n - 2) {
                     // the ring's accumulators of the last round and of the
                     // launch after it
@@ -436,7 +471,13 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
             for (int r = 0; r < ROWS; ++r) {
                 if (!col_ok || yb + r >= g.h) continue;
                 const size_t pi = static_cast<size_t>(yb + r) * g.w + x;
-                if constexpr (VEC == 4) {
+                if (kConv && (round == 0 || !all_here)) {
+                    // (the next round's may come from another workgroup: these
+                    // are in memory before this round's words)
+                    store_through<VEC>(g.labels, static_cast<size_t>(g.w) * g.h, pi, [&](int v) {
+                        return static_cast<unsigned>(kidx[cellv[r][v]]);
+                    });
+                } else if constexpr (VEC == 4) {
                     store_i4(labels + pi, kidx[cellv[r][0]], kidx[cellv[r][1]], kidx[cellv[r][2]],
                              kidx[cellv[r][3]]);
                 } else if constexpr (VEC == 2) {
@@ -449,6 +490,7 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
         if (sums_out) {
             accumulate<VEC, ROWS>(bins + (threadIdx.x & (kCopies - 1)) * bin_stride(ncells), ncells,
                                   cellv, pl, pa, pb, tx * VEC, ty * ROWS, col_ok ? g.h - yb : 0);
+            if (kConv && (round == 0 || !all_here)) __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
             if (i < ncells) {
                 unsigned long long p = 0;
@@ -497,39 +539,56 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
             }
         }
         __syncthreads();  // the bins are read
-
-        // ---- the next round, or the next tile that is this workgroup's
-        if (first) {
-            if (threadIdx.x < 64) take_census(a, s_words);
-            __syncthreads();
-            const int nwords = (a.n_tiles + kCensusBits - 1) / kCensusBits;
-            for (int j = 0; j < nwords; ++j) {
-                const unsigned b = s_words[j];
-                n_here += __popc(b);
-                if (j < me / kCensusBits) my_place += __popc(b);
-                if (j == me / kCensusBits) my_place += __popc(b & ((1u << (me % kCensusBits)) - 1u));
-            }
-            all_here = n_here == a.n_tiles;
-            if (!all_here) T = -1;
+        if constexpr (kConv) {
+            if (last && T == 0 && threadIdx.x == 0 && a.rounds_run) *a.rounds_run = a.n;
         }
-        if (all_here) {
+        return true;
+    };
+    for (bool first = true;; first = false) {
+        if (!(first && late) && !pass()) break;
+        if (first) {
+            if (threadIdx.x < 64) take_census(a, late ? 0 : kCensusTicks, s_words);
+            __syncthreads();
+            absent = a.n_tiles;
+            for (int j = 0; j * kCensusBits < a.n_tiles; ++j)
+                absent -= __popc(__builtin_amdgcn_readfirstlane(s_words[j]));
+            all_here = absent == 0;
+        }
+        if (all_here) {  // the same tile again
             if (++round == a.n) break;
             continue;
         }
-        bool mine = false;
-        while (!mine && round < a.n) {
-            if (++T == a.n_tiles) {
-                T = 0;
-                if (++round == a.n) break;
+        // the next pair that nobody has: the first round of the absent
+        // workgroups' tiles, then round by round all tiles; a.n at most, a
+        // workgroup's share, so that the chip's other users come in between
+        if (taken++ == a.n) break;
+        if (threadIdx.x == 0)
+            s_ticket = static_cast<int>(__hip_atomic_fetch_add(as_global(a.census) + kTicket, 1ull,
+                                                               __ATOMIC_RELAXED,
+                                                               __HIP_MEMORY_SCOPE_AGENT));
+        __syncthreads();
+        int q = __builtin_amdgcn_readfirstlane(s_ticket);
+        if (q >= absent) {
+            round = 1 + (q - absent) / a.n_tiles;
+            T = (q - absent) % a.n_tiles;
+            if (round >= a.n) break;
+        } else {
+            round = 0;
+            for (int j = 0;; ++j) {
+                const int in_word = min(a.n_tiles - j * kCensusBits, kCensusBits);
+                unsigned missing = ((1u << in_word) - 1u) &
+                                   ~__builtin_amdgcn_readfirstlane(s_words[j]);
+                const int c = __popc(missing);
+                if (q >= c) {
+                    q -= c;
+                    continue;
+                }
+                while (q--) missing &= missing - 1u;
+                T = j * kCensusBits + __builtin_ctz(missing);
+                break;
             }
-            const bool here = (s_words[T / kCensusBits] >> (T % kCensusBits)) & 1u;
-            mine = here ? T == me && round > 0 : T % n_here == my_place;
         }
-        if (!mine) break;
         enter(T);
-    }
-    if constexpr (kConv) {
-        if (my_place == 0 && threadIdx.x == 0 && a.rounds_run) *a.rounds_run = min(round, a.n);
     }
 }
 
@@ -677,7 +736,7 @@ hipError_t launch_rounds(const Workspace& ws, int32_t w, int32_t h, const Grid& 
     if (n < 2 || n > kMaxRounds || !rounds_args(ws, w, h, g, variant, cus, &a, &sources))
         return hipErrorInvalidValue;
     // workgroups said to take part must be able to run together
-    if (test && (a.n_tiles > cus ||
+    if (test && (a.n_tiles > 2 * cus ||
                  !(((1u << std::min(a.n_tiles, kCensusBits)) - 1u) & ~test->absent)))
         return hipErrorInvalidValue;
     a.g = assign_image(ws, w, h, g, variant);

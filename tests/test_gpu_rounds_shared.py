@@ -50,7 +50,7 @@ def variant(slic):
 
 
 SHAPES = [(64, 48, 8, 0), (97, 75, 8, 0), (300, 200, 16, 0), (333, 51, 27, 3), (640, 480, 16, 5),
-          (480, 320, 10, 7)]
+          (480, 320, 10, 7), (1024, 1024, 8, 5)]
 
 
 @pytest.mark.parametrize("squared", [False, True])

@@ -1,0 +1,96 @@
+"""Frames on several streams at once, whose rounds launches (csrc/rounds.hip)
+do not all fit the chip together: the results are those of one stream, and a
+frame takes at most twice the time that it takes alone (it took three to seven
+times that when a launch went on with only the workgroups that had started
+within 20 us)."""
+import time
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def slic():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    import paper_1509_04232_amd as slic
+    return slic
+
+
+def _gpu(img):
+    return torch.from_numpy(np.ascontiguousarray(img).reshape(-1)).cuda()
+
+
+@pytest.mark.parametrize("w,h,S,iters,enforce,streams", [
+    (1920, 1080, 8, 10, True, 2), (1920, 1080, 16, 4, False, 2), (1280, 720, 16, 10, True, 2),
+    (1280, 720, 16, 10, True, 4), (1600, 900, 16, 10, False, 4), (640, 480, 16, 10, True, 4),
+])
+def test_frames_on_streams(slic, w, h, S, iters, enforce, streams):
+    p = slic.Params(w, h, S=S, m=10.0)
+    cp = p.c()
+    rgb = [_gpu(synth.voronoi_image(i, w, h, w * h // 900, 8.0)) for i in range(streams)]
+    ws = [slic.workspace_for(p) for _ in rgb]
+    out = [torch.empty((h, w), dtype=torch.int32, device="cuda") for _ in rgb]
+    nseg = torch.zeros(streams, dtype=torch.int32, device="cuda")
+    side = [torch.cuda.Stream() for _ in rgb]
+
+    def frame(i, stream):
+        slic.slic_segment(cp, rgb[i].data_ptr(), iters, int(enforce), out[i].data_ptr(), None, None,
+                          nseg.data_ptr() + 4 * i if enforce else None, stream.cuda_stream,
+                          ws[i].data_ptr(), ws[i].numel())
+
+    def time_frames(n):
+        torch.cuda.synchronize()
+        best = 1e9
+        for _ in range(4):  # the first warms up
+            t0 = time.perf_counter()
+            for _ in range(20):
+                for i in range(n):
+                    frame(i, side[i])
+            torch.cuda.synchronize()
+            best = min(best, (time.perf_counter() - t0) / (20 * n))
+        return best
+
+    want = []
+    for i in range(streams):
+        frame(i, side[i])
+        torch.cuda.synchronize()
+        want.append(out[i].clone())
+        out[i].fill_(-1)
+    together = time_frames(streams)
+    for i in range(streams):
+        assert torch.equal(out[i], want[i]), i
+    alone = time_frames(1)
+    assert together < 2.0 * alone, f"{together * 1e6:.1f} us a frame, {alone * 1e6:.1f} us alone"
+
+
+def test_convergence_stop_on_streams(slic):
+    w, h, S, threshold = 1024, 768, 8, 0.5
+    p = slic.Params(w, h, S=S, m=10.0)
+    imgs = [synth.voronoi_image(40 + i, w, h, 800, 8.0) for i in range(4)]
+    want = [oracle.kmeans_converge(oracle.rgb_to_lab(i), S, 10.0, True, 12, threshold) for i in imgs]
+    rgb = [_gpu(i) for i in imgs]
+    side = [torch.cuda.Stream() for _ in imgs]
+    torch.cuda.synchronize()
+    for _ in range(5):
+        ctxs, done = [], []
+        for i, s in enumerate(side):
+            with torch.cuda.stream(s):
+                ctxs.append(slic.Context(p, rgb[i]))
+                done.append(ctxs[-1].iterate_converge(12, threshold))
+        torch.cuda.synchronize()
+        for i, s in enumerate(side):
+            with torch.cuda.stream(s):
+                lb, (cen, cnt) = ctxs[i].labels(), ctxs[i].centres()
+            torch.cuda.synchronize()
+            assert int(done[i].cpu()[0]) == want[i][3]
+            assert np.array_equal(lb.cpu().numpy(), want[i][0])
+            assert np.array_equal(cen.cpu().numpy(), want[i][1])
+            assert np.array_equal(cnt.cpu().numpy(), want[i][2])
+            ctxs[i].close()
