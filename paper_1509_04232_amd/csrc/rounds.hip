@@ -703,8 +703,13 @@ bool rounds_args(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int v
 // loaded or launched per round and a frame's slowest compute unit sets its
 // pace.  Per round, in us: 320 x 240 3.06 with 32 x 8 tiles, 3.15 with 32 x 16,
 // 3.93 with 64 x 16; 640 x 480 4.24 with 32 x 16, 5.05 with 64 x 16 (300 tiles
-// on 256 units); 800 x 600 4.63 and 4.95; 1024 x 1024 7.6 with 64 x 32, 8.9
-// with 64 x 16.
+// on 256 units); 1024 x 1024 7.6 with 64 x 32, 8.9 with 64 x 16.
+// More than 2.5 tiles per unit only where no larger tile of the table avoids
+// it: up to there two frames on different streams run side by side, beyond
+// it one waits for the other.  A frame of ten rounds with clean-up, in us, on
+// one and on four streams: 720 x 576 97 and 85 with 32 x 16 tiles (828), 102
+// and 40 with 32 x 32 (414); 1280 x 720 131 and 139 with 64 x 16 (900), 137 and
+// 84 with 64 x 32 (460).
 int rounds_variant(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int variant, int n) {
     if (n < kMinRounds || n > kMaxRounds) return 0;
     RoundsArgs a;
@@ -712,8 +717,11 @@ int rounds_variant(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int
     const long long px = static_cast<long long>(w) * h;
     const int cus = compute_units();
     if (variant == assign_default_variant(w, h, g.S)) {
-        if (px <= (1ll << 17) && rounds_args(ws, w, h, g, 1, cus, &a, &sources)) return 1;
-        if (px <= (1ll << 19) && rounds_args(ws, w, h, g, 2, cus, &a, &sources)) return 2;
+        const int smallest = px <= (1ll << 17) ? 1 : px <= (1ll << 19) ? 2 : variant;
+        const int order[] = {smallest, 3, 5};
+        for (const int v : order)
+            if (rounds_args(ws, w, h, g, v, cus, &a, &sources) && 2 * a.n_tiles <= 5 * cus) return v;
+        if (rounds_args(ws, w, h, g, smallest, cus, &a, &sources)) return smallest;
     }
     return rounds_args(ws, w, h, g, variant, cus, &a, &sources) ? variant : 0;
 }

@@ -1,6 +1,6 @@
 """Frames on several streams at once, whose rounds launches (csrc/rounds.hip)
 do not all fit the chip together: the results are those of one stream, and a
-frame takes at most twice the time that it takes alone (it took three to seven
+frame takes at most a given multiple of its time alone (it took three to seven
 times that when a launch went on with only the workgroups that had started
 within 20 us)."""
 import time
@@ -27,11 +27,14 @@ def _gpu(img):
     return torch.from_numpy(np.ascontiguousarray(img).reshape(-1)).cuda()
 
 
-@pytest.mark.parametrize("w,h,S,iters,enforce,streams", [
-    (1920, 1080, 8, 10, True, 2), (1920, 1080, 16, 4, False, 2), (1280, 720, 16, 10, True, 2),
-    (1280, 720, 16, 10, True, 4), (1600, 900, 16, 10, False, 4), (640, 480, 16, 10, True, 4),
+@pytest.mark.parametrize("w,h,S,iters,enforce,streams,most", [
+    (1920, 1080, 8, 10, True, 2, 2.0), (1920, 1080, 16, 4, False, 2, 2.0),
+    (1280, 720, 16, 10, True, 2, 2.0), (1600, 900, 16, 10, False, 4, 2.0),
+    (640, 480, 16, 10, True, 4, 2.0),
+    # frames of which two fit the chip (0.88 and 1.07 with smaller tiles)
+    (720, 576, 16, 10, True, 4, 0.8), (1280, 720, 16, 10, True, 4, 0.8),
 ])
-def test_frames_on_streams(slic, w, h, S, iters, enforce, streams):
+def test_frames_on_streams(slic, w, h, S, iters, enforce, streams, most):
     p = slic.Params(w, h, S=S, m=10.0)
     cp = p.c()
     rgb = [_gpu(synth.voronoi_image(i, w, h, w * h // 900, 8.0)) for i in range(streams)]
@@ -67,7 +70,7 @@ def test_frames_on_streams(slic, w, h, S, iters, enforce, streams):
     for i in range(streams):
         assert torch.equal(out[i], want[i]), i
     alone = time_frames(1)
-    assert together < 2.0 * alone, f"{together * 1e6:.1f} us a frame, {alone * 1e6:.1f} us alone"
+    assert together < most * alone, f"{together * 1e6:.1f} us a frame, {alone * 1e6:.1f} us alone"
 
 
 def test_convergence_stop_on_streams(slic):
