@@ -743,12 +743,12 @@ int slic_iterate_converge(slic_ctx* c, int32_t max_iters, float threshold,
     return SLIC_OK;
 }
 
-int slic_test_rounds(slic_ctx* c, int32_t n, uint32_t absent, float threshold,
+int slic_test_rounds(slic_ctx* c, int32_t n, uint32_t absent, int32_t polls, float threshold,
                      int32_t* d_iters_done) {
     if (!c || (d_iters_done && check_device_ptr(d_iters_done) != SLIC_OK)) return SLIC_EINVAL;
     if (c->state != 0) return SLIC_ESTATE;
     const int tiles = rounds_variant(c->ws, c->p.width, c->p.height, c->g, c->variant, n);
-    const RoundsTest test{absent};
+    const RoundsTest test{absent, polls};
     const RoundsStop stop{std::llrint(std::ldexp(static_cast<double>(threshold), kQShift)) *
                               static_cast<long long>(c->g.K),
                           d_iters_done};

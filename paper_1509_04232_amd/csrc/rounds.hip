@@ -45,6 +45,9 @@
 // words of a round before, all done.  (With the convergence stop, a workgroup
 // ends at the first pair it takes beyond the last round; a round has as many
 // pairs as there are workgroups, so none takes one of the round after.)
+// All that supposes that nobody else writes the words.  Two calls in one
+// workspace at once may clear them under a running launch; their results are
+// then wrong, but no thread polls more than kPolls times.
 #include "assign_tile.h"
 
 #include <algorithm>
@@ -61,6 +64,7 @@ constexpr int kMaxTiles = 1024;
 constexpr int kMaxWords = (kMaxTiles + kCensusBits - 1) / kCensusBits;
 constexpr long long kCensusTicks = 2000;  // of the 100 MHz clock: 20 us
 constexpr unsigned long long kFrozen = 1ull << 63;
+constexpr int kPolls = 1 << 23;  // of a thread in one launch: seconds
 constexpr int kMaxCells = 64;                     // per window
 constexpr int kFewSources = 6, kMaxSources = 16;  // tiles that a cell's sums are read from
 constexpr int kCopies = 4;  // of the bins
@@ -98,6 +102,7 @@ struct RoundsArgs {
     int sums_last;    // the last round adds its sums to the ring
     long long limit;     // convergence stop: after a round whose shift is below it
     unsigned long long* shift;  // two buffers of n_tiles words, zero before the launch
+    int polls;                  // after so many a thread waits no longer
     unsigned long long* wide;   // the same, not cleared: read only where a shift word says so
     int32_t* rounds_run;        // with converge (may be null)
 };
@@ -287,6 +292,7 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
     bool all_here = true;  // false: the census was frozen
     int absent = 0;        // workgroups not in it
     int taken = 0;         // pairs from the counter
+    int polls = a.polls;   // left to this thread
     int T = me;
     int round = 0;  // association a.t0 + round
     int checked = 0;  // rounds whose shift has been looked at
@@ -314,7 +320,8 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
                 unsigned long long total = sum_of_tiles([&](int j) {
                     unsigned long long v;
                     while ((v = agent_load<unsigned long long>(in + j)) >> (32 + kTagShift) !=
-                           static_cast<unsigned>(round)) {
+                               static_cast<unsigned>(round) &&
+                           --polls > 0) {
                     }
                     return v & kPayload;
                 });
@@ -365,7 +372,7 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
 #pragma unroll
                     for (int m = 0; m < SRC; ++m)
                         off |= static_cast<unsigned>(w[m] >> 32) ^ (static_cast<unsigned>(round) << kTagShift);
-                    if ((off >> kTagShift) == 0) break;
+                    if ((off >> kTagShift) == 0 || --polls <= 0) break;
                 }
                 unsigned long long sum = 0;
                 unsigned sum_y = 0;
@@ -759,6 +766,7 @@ hipError_t launch_rounds(const Workspace& ws, int32_t w, int32_t h, const Grid& 
             reinterpret_cast<uint4*>(a.census), words / 4);
     }
     if (test) freeze_census_kernel<<<1, 64, 0, s>>>(a.census, a.n_tiles, test->absent);
+    a.polls = test && test->polls > 0 ? test->polls : kPolls;
     a.limit = stop ? stop->limit : 0;
     a.rounds_run = stop ? stop->rounds_run : nullptr;
     return rounds_fn(variant, g.dist, sources, stop != nullptr)(a, s);

@@ -168,7 +168,8 @@ hipError_t launch_assign_final_ccl(const Workspace& ws, int32_t w, int32_t h, co
 // and write the rounds run (device int32, may be null).
 // test: a launch some of whose workgroups come too late to take part, as on a
 // shared chip: the workgroups b with bit b % 31 of `absent` (not for a frame
-// with more tiles than compute units, nor without any that takes part).
+// with more tiles than two per compute unit, nor without any that takes part);
+// polls: a thread's limit in place of the built-in one (0: that one).
 constexpr int kMinRounds = 2;
 struct RoundsStop {
     long long limit;
@@ -176,6 +177,7 @@ struct RoundsStop {
 };
 struct RoundsTest {
     uint32_t absent;
+    int32_t polls;
 };
 int rounds_variant(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int variant, int n);
 uint32_t* rounds_clear(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int variant,
@@ -295,7 +297,6 @@ struct slic_ctx {
 
 // For the tests, no part of the ABI: slic_iterate(ctx, n), or with threshold
 // >= 0 slic_iterate_converge(ctx, n, threshold, d_iters_done), as one rounds
-// launch without the workgroups that RoundsTest::absent names; SLIC_EINVAL
-// where the frame has no such launch.
-extern "C" int slic_test_rounds(slic_ctx* ctx, int32_t n, uint32_t absent, float threshold,
-                                int32_t* d_iters_done);
+// launch as RoundsTest says; SLIC_EINVAL where the frame has no such launch.
+extern "C" int slic_test_rounds(slic_ctx* ctx, int32_t n, uint32_t absent, int32_t polls,
+                                float threshold, int32_t* d_iters_done);

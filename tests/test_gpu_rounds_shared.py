@@ -25,11 +25,12 @@ def slic():
     return slic
 
 
-def _rounds(slic, ctx, n, absent, threshold=-1.0):
+def _rounds(slic, ctx, n, absent, threshold=-1.0, polls=0):
     fn = slic._abi.lib.slic_test_rounds
-    fn.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_uint32, ctypes.c_float, ctypes.c_void_p]
+    fn.argtypes = [ctypes.c_void_p, ctypes.c_int32, ctypes.c_uint32, ctypes.c_int32, ctypes.c_float,
+                   ctypes.c_void_p]
     done = torch.full((1,), -1, dtype=torch.int32, device="cuda")
-    assert fn(ctx.ctx, n, absent, threshold, done.data_ptr()) == slic.SLIC_OK
+    assert fn(ctx.ctx, n, absent, polls, threshold, done.data_ptr()) == slic.SLIC_OK
     return done
 
 
@@ -127,3 +128,31 @@ def test_clusters_that_empty_after_they_moved(slic, variant, w, h, S, v, m):
         assert np.array_equal(got.cpu().numpy(), cen)
         assert np.array_equal(n.cpu().numpy(), cnt)
         ctx.close()
+
+
+@pytest.mark.parametrize("squared", [False, True])
+@pytest.mark.parametrize("threshold", [-1.0, 0.0])
+@pytest.mark.parametrize("absent", [0x0, 0x55555555])
+@pytest.mark.parametrize("w,h,S,v", SHAPES[:3] + SHAPES[4:5])
+def test_waits_end_without_the_words(slic, variant, w, h, S, v, absent, threshold, squared):
+    """A thread that has polled its share goes on with what it has read (words
+    are only missing where another call uses the workspace at the same time):
+    the launch ends, every label is a cluster, and the frame after it is right."""
+    img = synth.voronoi_image(w + S, w, h, max(2, w * h // 900), 8.0)
+    p = slic.Params(w, h, S=S, m=10.0, squared_distance=squared)
+    variant(w, h, S, v)
+    ws = slic.workspace_for(p)
+    ctx = slic.Context(p, _gpu(img), workspace=ws)
+    _rounds(slic, ctx, 9, absent, threshold, polls=1)
+    lb = ctx.labels()
+    torch.cuda.synchronize()
+    assert 0 <= int(lb.min()) and int(lb.max()) < p.n_clusters
+    ctx.close()
+    dist = oracle.DIST_SQUARED if squared else oracle.DIST_EQ1
+    want = oracle.segment(img, S, 10.0, 3, True, False, 0, oracle.COLOR_LAB, dist)
+    ctx = slic.Context(p, _gpu(img), workspace=ws)
+    ctx.iterate(3)
+    lb = ctx.labels()
+    torch.cuda.synchronize()
+    assert np.array_equal(lb.cpu().numpy(), want["labels"])
+    ctx.close()
