@@ -69,3 +69,24 @@ def test_far_given_centres_converge(slic, squared, w, h, S, m, far, every, thres
     assert np.array_equal(got.cpu().numpy(), want[1])
     assert np.array_equal(cnt.cpu().numpy(), want[2])
     ctx.close()
+
+
+@pytest.mark.parametrize("w,h,S,threshold", [(320, 240, 16, 2.0), (333, 251, 27, 2.0),
+                                             (700, 500, 8, 3.0), (640, 480, 16, 1.2)])
+def test_squared_distance_stops_by_the_rule(slic, w, h, S, threshold):
+    """The rounds run from seeds under the squared distance, from the rule
+    itself (the oracle's own loop with the stop is stated for Eq. 1)."""
+    img = synth.voronoi_image(7 * w + S, w, h, max(2, w * h // 900), 8.0)
+    lab = oracle.rgb_to_lab(img)
+    seeds = oracle.kmeans(lab, S, 10.0, True, 0)[1]
+    want = compose(lab, S, 10.0, seeds, oracle.DIST_SQUARED, threshold)
+    ctx = slic.Context(slic.Params(w, h, S=S, m=10.0, squared_distance=True),
+                       torch.from_numpy(np.ascontiguousarray(img).reshape(-1)).cuda())
+    n = ctx.iterate_converge(MAX_ROUNDS, threshold)
+    lb, (got, cnt) = ctx.labels(), ctx.centres()
+    torch.cuda.synchronize()
+    assert int(n.cpu()[0]) == want[3]
+    assert np.array_equal(lb.cpu().numpy(), want[0])
+    assert np.array_equal(got.cpu().numpy(), want[1])
+    assert np.array_equal(cnt.cpu().numpy(), want[2])
+    ctx.close()
