@@ -128,8 +128,9 @@ int slic_iterate(slic_ctx* ctx, int32_t n_iters);
  * centres and their five components (L, a, b, x, y) with each |difference|
  * rounded to a multiple of 2^-18, is below threshold * K (threshold: the
  * mean shift per centre, >= 0), at most max_iters rounds.  The round that
- * meets the rule still associates.  The decision is taken on the device
- * (later launches exit at once), so nothing synchronises the host;
+ * meets the rule still associates.  The decision is taken on the device (one
+ * launch stops its rounds, or later launches exit at once), so nothing
+ * synchronises the host;
  * *d_iters_done (device int32, may be NULL) receives the rounds run.
  * Afterwards the context is final: slic_iterate returns SLIC_ESTATE, the
  * energy, copies and connectivity remain available. */
@@ -297,7 +298,7 @@ typedef struct {
 int32_t slic_net_param_count(int32_t S);
 
 /* Device workspace of the net calls below for n_crops (1..32) crops of
- * crop_w x crop_h pixels at grid step S (about 330 bytes per pixel); 0 if the
+ * crop_w x crop_h pixels at grid step S (about 300 bytes per pixel); 0 if the
  * shape is invalid. */
 size_t slic_net_workspace_bytes(int32_t n_crops, int32_t crop_w, int32_t crop_h, int32_t S);
 

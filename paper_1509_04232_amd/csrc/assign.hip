@@ -302,7 +302,7 @@ __global__ __launch_bounds__(kThreads, DIST == 0 ? 4 : 1) void assign_kernel(
         for (int i = threadIdx.x; i < ncells; i += kThreads) {
             const int row = static_cast<int>((static_cast<float>(i) + 0.5f) * inv_ncx);
             const int cx = gx_lo + (i - row * ncx), cy = gy_lo + row;
-                if (cx < 0 || cy < 0 || cx >= g.ns_c || cy >= g.ns_r) {
+            if (cx < 0 || cy < 0 || cx >= g.ns_c || cy >= g.ns_r) {
                 // no centre here: an infinite colour distance never wins
                 cen4[i] = make_float4(__builtin_huge_valf(), 0.0f, 0.0f, 0.0f);
                 ceny[i] = 0.0f;

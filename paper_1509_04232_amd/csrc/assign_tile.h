@@ -13,11 +13,14 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr unsigned kCertify = 160;  // distance of two keys
-// Infinite distance, the last slot: bounds the second key, so that an
-// infinite or undefined distance is never certified as the best (a given
-// centre may lie so far out that its distances overflow, and with m = 0 its
-// spatial term is then 0 * inf; the cells outside the grid would win).  The
-// keys have no sign, so that an undefined distance comes after an infinite one.
+// Infinite distance, the last slot: bounds the second key.  A given centre may
+// lie so far out that its distances overflow, and with m = 0 its spatial term
+// is then 0 * inf.  Under Eq. 1 an infinite or undefined distance is then never
+// certified as the best (the cells outside the grid would win), and the pixel
+// stays in its own cell.  Under the squared-sum distance an infinite one is not
+// settled either; where all nine are undefined (no cell outside the grid among
+// them) the first is taken.  The keys have no sign, so that an undefined
+// distance comes after an infinite one.
 constexpr unsigned kNoKey = 0x7F80000Fu, kKeyBits = 0x7FFFFFF0u;
 
 // Reference Eq. 1 distance: the exact operation sequence of the definition.
@@ -44,18 +47,6 @@ __device__ __forceinline__ unsigned umin3(unsigned a, unsigned b, unsigned c) {
 }
 __device__ __forceinline__ unsigned umed3(unsigned a, unsigned b, unsigned c) {
     return max(min(a, b), min(max(a, b), c));
-}
-
-// Global (device) memory as a named address space: accesses through such
-// pointers compile to global rather than flat memory instructions (flat ones
-// also count against the LDS wait counter, so every LDS wait would wait for
-// them too).
-template <class T>
-using gmem = __attribute__((address_space(1))) T;
-
-template <class T>
-__device__ __forceinline__ gmem<T>* as_global(T* p) {
-    return (gmem<T>*)p;
 }
 
 // 16-byte global accesses (builtin vector types: HIP's float4 and int4 are
@@ -209,8 +200,9 @@ __device__ __forceinline__ void add_bin(unsigned long long* bins, int ncells, in
 // where two fast values are too near to certify it; the squared-sum distance
 // is computed exactly, so only where the two smallest agree in all the bits
 // that a key keeps (keys of 32 bits for 64 took 154 instructions per pixel for
-// 189, and a 1080p frame of ten rounds 179 us for 193).  (All rows of a thread against one load of each candidate
-// took 8 instructions per pixel less, and more time: 104 registers for 86.)
+// 189, and a 1080p frame of ten rounds 179 us for 193).  (All rows of a thread
+// against one load of each candidate took 8 instructions per pixel less, and
+// more time: 104 registers for 86.)
 template <int VEC, int DIST>
 __device__ __forceinline__ void find_row(const float4* cen4, const float* ceny, int ncx, int base,
                                          float wgt, int x, int y, const float (&pl)[VEC],

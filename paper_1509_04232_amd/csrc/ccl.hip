@@ -25,18 +25,6 @@ namespace {
 
 constexpr int kBlock = 256;
 
-// Global (device) memory as a named address space.  Descriptors read from
-// a batch table hold generic pointers; accesses through them would compile
-// to flat instructions, which also count against the LDS wait counter, so
-// every kernel takes its arrays as global-address-space pointers.
-template <class T>
-using gmem = __attribute__((address_space(1))) T;
-
-template <class T>
-__device__ __forceinline__ gmem<T>* as_global(T* p) {
-    return (gmem<T>*)p;
-}
-
 __device__ __forceinline__ int load_relaxed(gmem<int>* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

@@ -10,9 +10,10 @@
 // the order written; the file is compiled without FMA contraction (the cube
 // root's fused multiply-adds are explicit).  The cube root's result is that
 // of Newton's method as written below (newton_cbrt), rounded to FP32, reached
-// by a certified cheaper estimate wherever that provably rounds the same.  The colour-space option yields
-// XYZ scaled by 100 (same order, then the scaling) or the R, G, B bytes as
-// floats instead; the seeds and the gradient work on whichever planes.
+// by a certified cheaper estimate wherever that provably rounds the same.  The
+// colour-space option yields XYZ scaled by 100 (same order, then the scaling)
+// or the R, G, B bytes as floats instead; the seeds and the gradient work on
+// whichever planes.
 //
 // Seeds: the seed of cell (cx, cy) is the cell's middle pixel
 // x0 + (x1 - x0 - 1) / 2 (likewise in y), the cell spanning [x0, x1)
@@ -141,17 +142,6 @@ __device__ __forceinline__ float cie_f(float t) {
     return static_cast<float>(__builtin_fma(__builtin_fma(-116.0, q0, s), rcp, q0));
 }
 
-// Global (device) memory as a named address space: accesses through pointers
-// read from a table would compile to flat instructions, which also count
-// against the LDS wait counter, so every table lookup would wait for them.
-template <class T>
-using gmem = __attribute__((address_space(1))) T;
-
-template <class T>
-__device__ __forceinline__ gmem<T>* as_global(T* p) {
-    return (gmem<T>*)p;
-}
-
 struct Bytes {
     uint8_t r, g, b;
 };
@@ -220,8 +210,8 @@ constexpr int kSmallTW = 32, kSmallTH = 16, kSmallThreads = 512;
 // seven waves (the trap handler's 16 count too), so a compute unit only one
 // workgroup of 16 waves instead of two (590 us).
 template <bool kBatch, int TW, int TH, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_num_sgpr(80))) void lab_seed_kernel(LabSeedImage single, LabSeedTileMap map,
-                                                      LabTables tab) {
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_num_sgpr(80))) void lab_seed_kernel(
+    LabSeedImage single, LabSeedTileMap map, LabTables tab) {
     constexpr int kSW = TW + 2 * kHalo, kSH = TH + 2 * kHalo;  // staged tile
     constexpr int kSeedsPerPass = NT / 9;
     static_assert(NT >= 256, "the sRGB table is loaded by the first 256 threads");

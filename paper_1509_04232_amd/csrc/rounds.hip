@@ -6,8 +6,9 @@
 // code anew, the pixels' loads, and global atomics that drain at its end.
 // Here each workgroup keeps its tile's pixels in registers for all rounds and
 // waits only for the tiles whose pixels can lie in its window's cells.
-// A 640 x 480 frame with 10 rounds went from 114 to 94 us, 1920 x 1080 from
-// 282 to 230, 320 x 240 with 5 rounds from 39.3 to 27.0.
+// With a launch per round and with this one, in us: 640 x 480 with 10 rounds
+// 114 and 85, 1920 x 1080 280 and 226, 933 x 800 148 and 132, 320 x 240 with 5
+// rounds 38 and 27, 1024 x 1024 with the convergence stop 122 and 94.
 //
 // Sums between rounds: every tile stores, for each cell of its window, the
 // sums of its own pixels, and each tile adds up the few tiles that a cell's
@@ -17,9 +18,9 @@
 // Waiting.  Every stored word carries the round's number, and the reader
 // loads a cell's words until all carry it: one trip through memory per round
 // where a counter per tile (stores, wait for them, counter, wait for it,
-// loads) took three, 1.4 to 1.9 us more per round.  The words are written and read as
-// agent-scope relaxed atomics, which the XCDs' caches keep coherent.  A tile
-// overwrites in round t what others read in round t - 1; it has then seen
+// loads) took three, 1.4 to 1.9 us more per round.  The words are written and
+// read as agent-scope relaxed atomics, which the XCDs' caches keep coherent.  A
+// tile overwrites in round t what others read in round t - 1; it has then seen
 // words of round t - 1 from each of them, which they store after they have
 // read (who reads whom is symmetric: own cells at most two apart).
 //
@@ -45,6 +46,14 @@
 // words of a round before, all done.  (With the convergence stop, a workgroup
 // ends at the first pair it takes beyond the last round; a round has as many
 // pairs as there are workgroups, so none takes one of the round after.)
+// A frame alone on the chip never comes to that.  On a chip that several
+// streams share the pairs cost as much as the kept tiles (1920 x 1080 14 us a
+// round either way, 640 x 480 7.2 for 4.7), but a launch that fills the chip
+// lets no other kernel in: us per frame on one, two and four streams, with a
+// launch per round and with this one, 640 x 480 115, 66, 49 and 86, 50, 42;
+// 1024 x 1024 156, 90, 71 and 133, 89, 90; 1920 x 1080 272, 194, 179 and 222,
+// 233, 216.  (When late workgroups left, the few that were in time did the
+// whole frame: 1920 x 1080 1,270 us on two streams.)
 // All that supposes that nobody else writes the words.  Two calls in one
 // workspace at once may clear them under a running launch; their results are
 // then wrong, but no thread polls more than kPolls times.
@@ -66,7 +75,12 @@ constexpr long long kCensusTicks = 2000;  // of the 100 MHz clock: 20 us
 constexpr unsigned long long kFrozen = 1ull << 63;
 constexpr int kPolls = 1 << 23;  // of a thread in one launch: seconds
 constexpr int kMaxCells = 64;                     // per window
-constexpr int kFewSources = 6, kMaxSources = 16;  // tiles that a cell's sums are read from
+// Tiles that a cell's sums are read from: a step of up to about half of the
+// tile's height needs at most six.  The kernels for sixteen hold some forty
+// registers more and read ten words more per round: with them alone a
+// 1920 x 1080 frame takes 250 us for 226, 640 x 480 89.7 for 85.1 (320 x 240,
+// whose cells have twelve, 26.9).
+constexpr int kFewSources = 6, kMaxSources = 16;
 constexpr int kCopies = 4;  // of the bins
 // A stored word: the round (from 1) in its top 14 bits; below them a colour
 // sum plus 2^40 (a tile's sums are below 2^37), or the position sums x, y (19

@@ -43,6 +43,18 @@ inline Divisor make_divisor(int32_t d) {
     return r;
 }
 
+// Global (device) memory as a named address space: accesses through such
+// pointers compile to global rather than flat memory instructions (flat ones,
+// which pointers read from a table would give, also count against the LDS wait
+// counter, so every LDS wait would wait for them too).
+template <class T>
+using gmem = __attribute__((address_space(1))) T;
+
+template <class T>
+__device__ __forceinline__ gmem<T>* as_global(T* p) {
+    return (gmem<T>*)p;
+}
+
 struct Grid {
     int32_t S, ns_c, ns_r, K;
     float w;      // m / S in FP32, the factor of d_xy in Eq. 1
@@ -153,7 +165,7 @@ hipError_t launch_assign(const Workspace& ws, int32_t w, int32_t h, const Grid& 
 // it also writes the clean-up's tile-local components (ws.ccl0, ws.ccl3,
 // ws.ccl1, the connectivity pass's first step), so launch_connectivity then
 // runs with local_done.  Only where assign_final_ccl_supported (the launch
-// has the 1 x 4 shape, whose tiles are the clean-up's 32 x 32 tiles).
+// takes the clean-up's 32 x 32 tiles, one or four pixels wide per thread).
 bool assign_final_ccl_supported(int32_t w, int32_t h, int32_t S);
 hipError_t launch_assign_final_ccl(const Workspace& ws, int32_t w, int32_t h, const Grid& g,
                                   int64_t t, hipStream_t s);
