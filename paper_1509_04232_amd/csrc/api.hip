@@ -743,6 +743,14 @@ int slic_iterate_converge(slic_ctx* c, int32_t max_iters, float threshold,
     return SLIC_OK;
 }
 
+int slic_test_rounds_variant(const slic_params* p, int32_t n) {
+    if (!params_ok(p)) return -1;
+    Grid g;
+    compute_grid(p, &g);
+    return rounds_variant(Workspace{}, p->width, p->height, g,
+                          resolve_variant(p->width, p->height, g.S), n);
+}
+
 int slic_test_rounds(slic_ctx* c, int32_t n, uint32_t absent, int32_t polls, float threshold,
                      int32_t* d_iters_done) {
     if (!c || (d_iters_done && check_device_ptr(d_iters_done) != SLIC_OK)) return SLIC_EINVAL;

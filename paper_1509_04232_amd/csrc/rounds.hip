@@ -737,14 +737,15 @@ int rounds_variant(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int
     int sources = 0;
     const long long px = static_cast<long long>(w) * h;
     const int cus = compute_units();
-    if (variant == assign_default_variant(w, h, g.S)) {
-        const int smallest = px <= (1ll << 17) ? 1 : px <= (1ll << 19) ? 2 : variant;
-        const int order[] = {smallest, 3, 5};
-        for (const int v : order)
-            if (rounds_args(ws, w, h, g, v, cus, &a, &sources) && 2 * a.n_tiles <= 5 * cus) return v;
-        if (rounds_args(ws, w, h, g, smallest, cus, &a, &sources)) return smallest;
-    }
-    return rounds_args(ws, w, h, g, variant, cus, &a, &sources) ? variant : 0;
+    auto fits = [&](int v) { return rounds_args(ws, w, h, g, v, cus, &a, &sources); };
+    if (variant != assign_default_variant(w, h, g.S)) return fits(variant) ? variant : 0;
+    const int small[] = {1, 2, variant};  // by the frame's size
+    const int first = px <= (1ll << 17) ? 0 : px <= (1ll << 19) ? 1 : 2;
+    for (const int v : {small[first], std::max(small[first], 2), 3, 5})
+        if (fits(v) && 2 * a.n_tiles <= 5 * cus) return v;
+    for (int i = first; i < 3; ++i)
+        if (fits(small[i])) return small[i];
+    return 0;
 }
 
 uint32_t* rounds_clear(const Workspace& ws, int32_t w, int32_t h, const Grid& g, int variant,

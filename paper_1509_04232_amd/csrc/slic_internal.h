@@ -310,5 +310,8 @@ struct slic_ctx {
 // For the tests, no part of the ABI: slic_iterate(ctx, n), or with threshold
 // >= 0 slic_iterate_converge(ctx, n, threshold, d_iters_done), as one rounds
 // launch as RoundsTest says; SLIC_EINVAL where the frame has no such launch.
+// slic_test_rounds_variant: the tiles of such a launch of n rounds (pure host
+// but for the device's compute units: 256 without one).
+extern "C" int slic_test_rounds_variant(const slic_params* p, int32_t n);
 extern "C" int slic_test_rounds(slic_ctx* ctx, int32_t n, uint32_t absent, int32_t polls,
                                 float threshold, int32_t* d_iters_done);
