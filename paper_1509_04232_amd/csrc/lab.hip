@@ -197,6 +197,14 @@ constexpr int kThreads = 1024;
 // Smaller frames take 32 x 16 tiles, one pixel per thread: the time follows
 // the conversions of the busiest compute unit, and small tiles spread them.
 constexpr int kSmallTW = 32, kSmallTH = 16, kSmallThreads = 512;
+// Frames with more than two large tiles per compute unit take them with half
+// the threads (four pixels each): as fast alone (1920 x 1080 at S = 16 with four
+// rounds 82.2 us, 83.7 with 1,024 threads), and beside another stream's rounds
+// launch, whose workgroups leave their unit one by one, eight waves find room
+// sooner than sixteen (that frame on four streams 88 us for 113, 1920 x 1080 at
+// S = 8 with ten rounds 191 for 217).  With fewer tiles a unit is left half
+// empty (933 x 800: 132 us for 129).
+constexpr int kManyThreads = 512;
 
 // kBatch: the workgroup's image comes from the tile map (a batch) rather
 // than the kernel argument; separate instantiations, so a single-image
@@ -436,8 +444,11 @@ hipError_t launch_lab_seed(const uint8_t* rgb, int32_t w, int32_t h, int32_t pit
         lab_seed_kernel<false, kSmallTW, kSmallTH, kSmallThreads>
             <<<dim3(small_x, small_y), kSmallThreads, 0, s>>>(a, none, tables());
     } else {
-        dim3 g((w + kTW - 1) / kTW, (h + kTH - 1) / kTH);
-        lab_seed_kernel<false, kTW, kTH, kThreads><<<g, kThreads, 0, s>>>(a, none, tables());
+        const dim3 g((w + kTW - 1) / kTW, (h + kTH - 1) / kTH);
+        if (static_cast<long long>(g.x) * g.y > 2ll * compute_units())
+            lab_seed_kernel<false, kTW, kTH, kManyThreads><<<g, kManyThreads, 0, s>>>(a, none, tables());
+        else
+            lab_seed_kernel<false, kTW, kTH, kThreads><<<g, kThreads, 0, s>>>(a, none, tables());
     }
     return hipGetLastError();
 }

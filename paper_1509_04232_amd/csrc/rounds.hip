@@ -52,7 +52,7 @@
 // lets no other kernel in: us per frame on one, two and four streams, with a
 // launch per round and with this one, 640 x 480 115, 66, 49 and 86, 50, 42;
 // 1024 x 1024 156, 90, 71 and 133, 89, 90; 1920 x 1080 272, 194, 179 and 222,
-// 233, 216.  (When late workgroups left, the few that were in time did the
+// 228, 190.  (When late workgroups left, the few that were in time did the
 // whole frame: 1920 x 1080 1,270 us on two streams.)
 // All that supposes that nobody else writes the words.  Two calls in one
 // workspace at once may clear them under a running launch; their results are

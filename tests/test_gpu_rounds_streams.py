@@ -31,6 +31,8 @@ def _gpu(img):
     (1920, 1080, 8, 10, True, 2, 2.0), (1920, 1080, 16, 4, False, 2, 2.0),
     (1280, 720, 16, 10, True, 2, 2.0), (1600, 900, 16, 10, False, 4, 2.0),
     (640, 480, 16, 10, True, 4, 2.0),
+    # (1.35 while the conversion's workgroups of sixteen waves found no room)
+    (1920, 1080, 16, 4, False, 4, 1.2),
     # frames of which two fit the chip (0.88 and 1.07 with smaller tiles)
     (720, 576, 16, 10, True, 4, 0.8), (1280, 720, 16, 10, True, 4, 0.8),
 ])
