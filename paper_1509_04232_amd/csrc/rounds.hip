@@ -116,9 +116,9 @@ struct RoundsArgs {
     int sums_last;    // the last round adds its sums to the ring
     long long limit;     // convergence stop: after a round whose shift is below it
     unsigned long long* shift;  // two buffers of n_tiles words, zero before the launch
-    int polls;                  // after so many a thread waits no longer
     unsigned long long* wide;   // the same, not cleared: read only where a shift word says so
     int32_t* rounds_run;        // with converge (may be null)
+    int polls;                  // after so many a thread waits no longer
 };
 
 template <class T>
@@ -588,18 +588,22 @@ __global__ __launch_bounds__(kThreads, 4) void rounds_kernel(RoundsArgs a) {
                                                                __ATOMIC_RELAXED,
                                                                __HIP_MEMORY_SCOPE_AGENT));
         __syncthreads();
-        int q = __builtin_amdgcn_readfirstlane(s_ticket);
-        if (q >= absent) {
-            round = 1 + (q - absent) / a.n_tiles;
-            T = (q - absent) % a.n_tiles;
-            if (round >= a.n) break;
+        // (unsigned: in range for any value of the counter)
+        unsigned q = __builtin_amdgcn_readfirstlane(s_ticket);
+        const unsigned tiles = a.n_tiles;
+        if (absent <= 0 || q >= static_cast<unsigned>(absent)) {
+            q -= absent;
+            const unsigned r = q / tiles + 1u;
+            if (r >= static_cast<unsigned>(a.n)) break;
+            round = r;
+            T = q % tiles;
         } else {
             round = 0;
             for (int j = 0;; ++j) {
                 const int in_word = min(a.n_tiles - j * kCensusBits, kCensusBits);
                 unsigned missing = ((1u << in_word) - 1u) &
                                    ~__builtin_amdgcn_readfirstlane(s_words[j]);
-                const int c = __popc(missing);
+                const unsigned c = __popc(missing);
                 if (q >= c) {
                     q -= c;
                     continue;
