@@ -198,8 +198,8 @@ constexpr int kThreads = 1024;
 // the conversions of the busiest compute unit, and small tiles spread them.
 constexpr int kSmallTW = 32, kSmallTH = 16, kSmallThreads = 512;
 // Frames with more than two large tiles per compute unit take them with half
-// the threads (four pixels each): as fast alone (1920 x 1080 at S = 16 with four
-// rounds 82.2 us, 83.7 with 1,024 threads), and beside another stream's rounds
+// the threads (four pixels each): no slower alone (at 1920 x 1080 and S = 8 the
+// conversion takes 17.9 us for 19.4 with 1,024 threads), and beside another stream's rounds
 // launch, whose workgroups leave their unit one by one, eight waves find room
 // sooner than sixteen (that frame on four streams 88 us for 113, 1920 x 1080 at
 // S = 8 with ten rounds 191 for 217).  With fewer tiles a unit is left half
