@@ -31,10 +31,11 @@ def _gpu(img):
     (1920, 1080, 8, 10, True, 2, 2.0), (1920, 1080, 16, 4, False, 2, 2.0),
     (1280, 720, 16, 10, True, 2, 2.0), (1600, 900, 16, 10, False, 4, 2.0),
     (640, 480, 16, 10, True, 4, 2.0),
-    # (1.35 while the conversion's workgroups of sixteen waves found no room)
-    (1920, 1080, 16, 4, False, 4, 1.2),
-    # frames of which two fit the chip (0.88 and 1.07 with smaller tiles)
-    (720, 576, 16, 10, True, 4, 0.8), (1280, 720, 16, 10, True, 4, 0.8),
+    # (1.35 while the conversion's workgroups of sixteen waves found no room, now 1.07)
+    (1920, 1080, 16, 4, False, 4, 1.25),
+    # frames of which two fit the chip (0.88 and 1.07 with smaller tiles, now 0.4
+    # and 0.6 to 0.73)
+    (720, 576, 16, 10, True, 4, 0.75), (1280, 720, 16, 10, True, 4, 0.95),
 ])
 def test_frames_on_streams(slic, w, h, S, iters, enforce, streams, most):
     p = slic.Params(w, h, S=S, m=10.0)
