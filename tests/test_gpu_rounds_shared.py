@@ -156,3 +156,34 @@ def test_waits_end_without_the_words(slic, variant, w, h, S, v, absent, threshol
     torch.cuda.synchronize()
     assert np.array_equal(lb.cpu().numpy(), want["labels"])
     ctx.close()
+
+
+@pytest.mark.parametrize("far,threshold,want_rounds", [(1e10, 9e9, 2), (1e10, 2e10, 1), (2.0 ** 33, 1.0, None)])
+@pytest.mark.parametrize("absent", ABSENT)
+@pytest.mark.parametrize("w,h,S,v", [(97, 75, 8, 0), (300, 200, 16, 0), (333, 51, 27, 3)])
+def test_far_given_centres_without_all_workgroups(slic, variant, w, h, S, v, absent, far, threshold,
+                                                  want_rounds):
+    """Shifts too wide for their words, of tiles that change hands."""
+    img = synth.voronoi_image(w + S, w, h, max(2, w * h // 900), 8.0)
+    lab = oracle.rgb_to_lab(img)
+    cen = oracle.kmeans(lab, S, 10.0, True, 2)[1].copy()
+    cen[:, 3] += np.float32(far)
+    variant(w, h, S, v)
+    ctx = slic.Context(slic.Params(w, h, S=S, m=0.0), _gpu(img), centres=torch.from_numpy(cen).cuda())
+    n = _rounds(slic, ctx, 6, absent, threshold)
+    limit = int(np.rint(threshold * 2.0 ** 18)) * len(cen)
+    labels = oracle.assign(lab, S, 0.0, cen)
+    for rounds in range(1, 7):
+        prev = cen
+        cen, cnt = oracle.update(lab, labels, prev)
+        labels = oracle.assign(lab, S, 0.0, cen)
+        if oracle.residual(prev, cen) < limit:
+            break
+    assert want_rounds is None or rounds == want_rounds
+    lb, (got, counts) = ctx.labels(), ctx.centres()
+    torch.cuda.synchronize()
+    assert int(n.cpu()[0]) == rounds
+    assert np.array_equal(lb.cpu().numpy(), labels)
+    assert np.array_equal(got.cpu().numpy(), cen)
+    assert np.array_equal(counts.cpu().numpy(), cnt)
+    ctx.close()
